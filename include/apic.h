@@ -257,7 +257,12 @@ apic_status apic_gather_push(apic_ctx *ctx, apic_particles *p, const void *E, do
  * (slots come from per-bucket tallies, not from atomics), so repeated runs
  * give identical bits; the one exception is a particle that jumps more than
  * one tile in a step, which takes a slot at the end of its bucket in arrival
- * order. Workspace contents are not relied on across calls. */
+ * order. Calls of 8 steps or more (without perm, and with 512 particles or
+ * more per bucket on average) keep the particles in pages of the workspace
+ * between their steps and put them back in bucket order at the end: the same
+ * fields and particles, in another order inside the buckets than the same
+ * steps in shorter calls leave. Workspace contents are not relied on across
+ * calls. */
 apic_status apic_step(apic_ctx *ctx, apic_particles *p, void *rho, double *E, float *E32, int nsteps,
                       double *diag, void *ws, void *stream);
 
@@ -280,8 +285,10 @@ apic_status apic_step_pair(apic_ctx *ctx, apic_particles *p, apic_particles *q, 
  * APIC_STATIC_WS_BYTES bytes inside the library, one per GPU the library runs
  * on (held until the process ends); the call allocates nothing and otherwise
  * behaves as apic_step with that array as ws (the same kernels, results and
- * errors). Returns APIC_EINVAL, with a message, when the context's workspace
- * (apic_workspace_size) exceeds the array, and APIC_EUNSUPPORTED for 3D
+ * errors; where the array has room for the context's workspace only without
+ * the pages of long calls, every step reorders the particles). Returns
+ * APIC_EINVAL, with a message, when the workspace without those pages
+ * exceeds the array, and APIC_EUNSUPPORTED for 3D
  * contexts and 2D grids whose sides are not powers of two in [4, 1024] (their
  * field solve goes through the FFT library). Every call on one GPU uses that
  * GPU's one array, so calls that overlap on one GPU (other streams, other
@@ -293,7 +300,8 @@ apic_status apic_step_static(apic_ctx *ctx, apic_particles *p, void *rho, double
 
 /* Per-phase timing of apic_step with HIP events recorded on the caller's
  * stream around each phase of each step (count pass, scan, push pass, field
- * solve). apic_profile_enable(ctx, max_steps) creates the events (host call,
+ * solve; a step of a call that keeps the particles in pages has no count pass,
+ * and its exchange between the buckets is reported as the scan). apic_profile_enable(ctx, max_steps) creates the events (host call,
  * not for capture; max_steps = 0 disables); apic_profile_read waits for the
  * last event and returns the summed milliseconds per phase in ms[4] and the
  * number of profiled steps, then rearms. Steps beyond max_steps are not timed. */

@@ -815,7 +815,7 @@ AdjWs adj_layout(const apic_ctx *c, int stride) {
     const int dim = c->d.dim, vdim = c->d.vdim;
     size_t off = 0;
     auto take = [&](size_t b) { size_t o = off; off = align256(off + b); return o; };
-    L.ctx = take(c->ws_bytes);
+    L.ctx = take(c->ws_step_bytes);
     for (auto &v : L.pw_pos) v = (size_t)-1;
     for (auto &v : L.pw_vel) v = (size_t)-1;
     if (c->mixed) {

@@ -107,36 +107,38 @@ void default_tiles(const apic_grid_desc &d, int64_t n, int &tsx, int &tsy, int &
     }
 }
 
+// Pages of the paged storage (0: the context's calls always reorder). Twice
+// what the particles can occupy, ceil(n / kPage) full pages and one partly
+// filled per bucket: a step takes pages only from those free before it, and
+// in the worst case (every bucket empties into another) it takes as many as
+// are in use. Not used where a bucket holds fewer than four pages on average
+// (the pool would be mostly padding), and below the limits of its 32-bit slot
+// indices and of the workspace it may add.
+constexpr int64_t kPagedMaxN = int64_t(1) << 28;
+
+int64_t pages_wanted(const apic_ctx *c) {
+    const int64_t nb = c->g.nbuckets;
+    if (c->n < 4 * kPage * nb || c->n > kPagedMaxN) return 0;
+    return 2 * ((c->n + kPage - 1) / kPage + nb);
+}
+
+// Bytes of one particle's state.
+size_t particle_bytes(const apic_ctx *c) {
+    return c->mixed ? 4 * (1 + c->d.dim + c->d.vdim) : 8 * (c->d.dim + c->d.vdim);
+}
+
+// Entries of the outbox (its pieces of 16 bytes stay aligned).
+int64_t paged_slots(int64_t n) { return (n + 3) / 4 * 4; }
+
 void layout(apic_ctx *c) {
     const int64_t n = c->n;
-    const size_t r = c->mixed ? 4 : 8;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
     const int dim = c->d.dim, vdim = c->d.vdim;
-    c->o_x = c->o_y = c->o_z = c->o_cell = c->o_ox = c->o_oy = c->o_oz = (size_t)-1;
-    c->o_vx = c->o_vy = c->o_vz = (size_t)-1;
-    if (c->mixed) {
-        c->o_cell = take(4 * n);
-        c->o_ox = take(4 * n);
-        if (dim >= 2) c->o_oy = take(4 * n);
-        if (dim == 3) c->o_oz = take(4 * n);
-    } else {
-        c->o_x = take(8 * n);
-        if (dim >= 2) c->o_y = take(8 * n);
-        if (dim == 3) c->o_z = take(8 * n);
-    }
-    c->o_vx = take(r * n);
-    if (vdim >= 2) c->o_vy = take(r * n);
-    if (vdim >= 3) c->o_vz = take(r * n);
+    const size_t r = c->mixed ? 4 : 8;
     const int64_t nb = c->g.nbuckets;
     const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
-    c->o_keys = take(4 * n);
-    c->o_keys2 = take(4 * n);
-    c->o_idx = take(4 * n);
-    c->o_idx2 = take(4 * n);
-    c->o_rcnt = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
-    c->o_roff = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
-    c->o_rpart = take(4 * (int64_t)sort_part_entries());
+    // what every step uses
     c->o_bstart = take(4 * (nb + 1));
     c->o_cnt = take(4 * nb * kStepTab);
     c->o_offs = take(4 * nb * kStepTab);
@@ -159,9 +161,105 @@ void layout(apic_ctx *c) {
     } else {
         c->o_rhat = c->o_ehat = (size_t)-1;
     }
-    c->ws_bytes = off;
+    const size_t common = off;
+    // the sort and the reordering step: the second particle buffer, sort arrays
+    c->o_x = c->o_y = c->o_z = c->o_cell = c->o_ox = c->o_oy = c->o_oz = (size_t)-1;
+    c->o_vx = c->o_vy = c->o_vz = (size_t)-1;
+    if (c->mixed) {
+        c->o_cell = take(4 * n);
+        c->o_ox = take(4 * n);
+        if (dim >= 2) c->o_oy = take(4 * n);
+        if (dim == 3) c->o_oz = take(4 * n);
+    } else {
+        c->o_x = take(8 * n);
+        if (dim >= 2) c->o_y = take(8 * n);
+        if (dim == 3) c->o_z = take(8 * n);
+    }
+    c->o_vx = take(r * n);
+    if (vdim >= 2) c->o_vy = take(r * n);
+    if (vdim >= 3) c->o_vz = take(r * n);
+    c->o_keys = take(4 * n);
+    c->o_keys2 = take(4 * n);
+    c->o_idx = take(4 * n);
+    c->o_idx2 = take(4 * n);
+    c->o_rcnt = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
+    c->o_roff = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
+    c->o_rpart = take(4 * (int64_t)sort_part_entries());
+    c->ws_step_bytes = c->ws_bytes = off;
+    c->npages = pages_wanted(c);
+    if (!c->npages) return;
+    // the paged storage, in the place of those (none of them is live in a paged call)
+    off = common;
+    const size_t state = particle_bytes(c);
+    c->o_pool = take((size_t)c->npages * kPage * state);
+    c->o_out = take(2 * (size_t)paged_slots(n) * state);
+    c->o_ptab = take(2 * 4 * c->npages);
+    c->o_pqueue = take(4 * c->npages);
+    c->o_phead = take(64);
+    c->o_praw = take(2 * 4 * n);
+    c->o_phole = take(2 * 4 * n);
+    c->o_pcode = take(2 * n);
+    c->o_porder = take(2 * 4 * n);
+    c->o_pfar = take(2 * 2 * 4 * n);
+    c->o_plcnt = take(2 * 4 * nb * kStepTab);
+    c->o_ploff = take(2 * 4 * nb * kStepTab);
+    c->o_pcnt = take(3 * 4 * nb);
+    c->o_pds = take(2 * 4 * (nb + 1));
+    c->o_pps = take(2 * 4 * (nb + 1));
+    c->ws_bytes = std::max(c->ws_bytes, off);
 }
 
+// Paged storage as the push of step k sees it: the counts rotate over three
+// buffers, the tables and lists over two.
+PageStep page_step(const apic_ctx *c, void *ws, int k) {
+    const int64_t nb = c->g.nbuckets, n = c->n;
+    const int a = k & 1, b = 1 - a, z = k % 3;
+    PageStep t{};
+    int32_t *cnt = wsp<int32_t>(ws, c->o_pcnt), *ds = wsp<int32_t>(ws, c->o_pds), *ps = wsp<int32_t>(ws, c->o_pps);
+    int32_t *tab = wsp<int32_t>(ws, c->o_ptab);
+    t.cnt_old = cnt + (z + 2) % 3 * nb;
+    t.cnt = cnt + z * nb;
+    t.cnt_next = cnt + (z + 1) % 3 * nb;
+    t.ds_old = ds + b * (nb + 1);
+    t.ds = ds + a * (nb + 1);
+    t.ps_old = ps + b * (nb + 1);
+    t.ps = ps + a * (nb + 1);
+    t.tab_old = tab + b * c->npages;
+    t.tab = tab + a * c->npages;
+    t.queue = wsp<int32_t>(ws, c->o_pqueue);
+    t.head = wsp<unsigned long long>(ws, c->o_phead);
+    t.npages = c->npages;
+    int32_t *words = (int32_t *)(t.head + 2);   // three far counters, the live count
+    t.live = words + 3;
+    t.nfar_clear = words + (z + 1) % 3;
+    t.pool = wsp<char>(ws, c->o_pool);
+    t.out_slots = paged_slots(n);
+    const size_t state = particle_bytes(c);
+    auto list = [&](int side, int nfar) {
+        PageList l{};
+        l.cnt = wsp<int32_t>(ws, c->o_plcnt) + side * nb * kStepTab;
+        l.off = wsp<int32_t>(ws, c->o_ploff) + side * nb * kStepTab;
+        l.raw_slot = wsp<int32_t>(ws, c->o_praw) + side * n;
+        l.raw_code = wsp<uint8_t>(ws, c->o_pcode) + side * n;
+        l.hole = wsp<int32_t>(ws, c->o_phole) + side * n;
+        l.order = wsp<int32_t>(ws, c->o_porder) + side * n;
+        l.far = wsp<int32_t>(ws, c->o_pfar) + side * 2 * n;
+        l.far_dest = l.far + n;
+        l.nfar = words + nfar;
+        l.out = wsp<char>(ws, c->o_out) + side * t.out_slots * state;
+        return l;
+    };
+    t.in = list(b, (z + 2) % 3);
+    t.to = list(a, z);
+    return t;
+}
+
+apic_status page_begin(apic_ctx *c, const int32_t *bstart, void *acc, int64_t nacc, void *ws, hipStream_t s) {
+    const PageStep t = page_step(c, ws, 0);
+    HIPCHK(c, launch_page_begin(c->g, t, wsp<int32_t>(ws, c->o_pcnt), (int32_t *)(t.head + 2), c->n, max_per_bucket(c),
+                                bstart, (uint64_t *)acc, nacc, c->dev, s));
+    return APIC_OK;
+}
 
 Parts parts_of(const apic_particles *p) {
     Parts q;
@@ -315,6 +413,12 @@ apic_status field_from_acc(apic_ctx *c, void *acc, bool acc_is_rho, double *E, f
     FFTCHK(c, hipfftExecZ2D(c->inv, (hipfftDoubleComplex *)ehat, (hipfftDoubleReal *)rho));
     HIPCHK(c, launch_grad(c->g, rho, E, E32, fin, c->dev, s));
     return APIC_OK;
+}
+
+hipEvent_t *profile_events(apic_ctx *c, bool paged) {
+    if (c->prof_used >= c->prof_max || c->prof_step++ % c->prof_every != 0) return nullptr;
+    c->ev_paged[c->prof_used] = paged;
+    return &c->ev[5 * (size_t)c->prof_used++];
 }
 
 apic_status copy_parts(apic_ctx *c, const Parts &dst, const Parts &src, hipStream_t s) {
@@ -679,11 +783,47 @@ apic_status apic_gather_push(apic_ctx *c, apic_particles *p, const void *E, doub
 
 namespace apic_host {
 
+// nsteps cycles on paged particles (apic_pages.hip): from p to dst and its
+// bucket table bs_dst (p itself, or the second buffer).
+apic_status step_paged(apic_ctx *c, apic_particles *p, const Parts &dst, int32_t *bs_dst, void *rho, double *E,
+                       float *E32, int nsteps, double *diag, void *ws, hipStream_t s) {
+    const int nb = c->g.nbuckets;
+    const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
+    void *acc = wsp<void>(ws, c->o_acc);
+    const Parts A = parts_of(p);
+    const PushC pc = push_coeffs(c, 1.0, 1);
+    float *e32 = c->o_e32 != (size_t)-1 ? wsp<float>(ws, c->o_e32) : nullptr;
+    apic_status st = page_begin(c, p->bucket_start, acc, G, ws, s);
+    if (st != APIC_OK) return st;
+    for (int k = 0; k < nsteps; ++k) {
+        const PageStep t = page_step(c, ws, k);
+        const bool last = k == nsteps - 1;
+        hipEvent_t *ev = profile_events(c, true);
+        if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
+        HIPCHK(c, launch_page_push(c->g, c->mixed, t, k == 0 ? &A : nullptr, p->bucket_start, c->n, max_per_bucket(c),
+                                   E, k > 0 ? e32 : nullptr, pc, acc, diag ? c->dev.part_push : nullptr, c->dev, s));
+        if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
+        if (rho && last) {
+            if (c->mixed)
+                HIPCHK(c, launch_copy_bytes(rho, acc, 8 * G, s));
+            else
+                HIPCHK(c, launch_rho(c->g, false, acc, (double *)rho, acc_scale(c), c->d.rho_ion, 0, nullptr, s));
+        }
+        st = field_from_acc(c, acc, false, (last || !e32) ? E : nullptr, last ? E32 : e32, diag, nullptr, nullptr,
+                            diag ? nb : 0, 1, ws, s, t.live);
+        if (st != APIC_OK) return st;
+        if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[4], s));
+    }
+    HIPCHK(c, launch_page_end(c->g, c->mixed, page_step(c, ws, nsteps), c->n, max_per_bucket(c), dst, bs_dst, c->dev, s));
+    return APIC_OK;
+}
+
 // nsteps cycles alternating between the particle buffers A (p, holding the
 // state on entry) and B with its bucket table bsB; after an odd count the
 // state is in B, and copy_back moves it to p.
+// ws_pages: ws holds the whole workspace, the paged storage included.
 apic_status step_run(apic_ctx *c, apic_particles *p, const Parts &B, int32_t *bsB, bool copy_back, void *rho,
-                     double *E, float *E32, int nsteps, double *diag, void *ws, hipStream_t s) {
+                     double *E, float *E32, int nsteps, double *diag, void *ws, bool ws_pages, hipStream_t s) {
     apic_status st = APIC_OK;
     const int nb = c->g.nbuckets;
     const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
@@ -693,6 +833,10 @@ apic_status step_run(apic_ctx *c, apic_particles *p, const Parts &B, int32_t *bs
     int32_t *tot = wsp<int32_t>(ws, c->o_tot);
     int32_t *deep = wsp<int32_t>(ws, c->o_deep);
     void *acc = wsp<void>(ws, c->o_acc);
+    if (nsteps >= kPagedSteps && c->npages && !p->perm && ws_pages) {
+        const bool to_b = (nsteps & 1) && !copy_back;
+        return step_paged(c, p, to_b ? B : parts_of(p), to_b ? bsB : p->bucket_start, rho, E, E32, nsteps, diag, ws, s);
+    }
     const Parts A = parts_of(p);
     int32_t *bsA = p->bucket_start;
     const PushC pc = push_coeffs(c, 1.0, 1);
@@ -712,8 +856,7 @@ apic_status step_run(apic_ctx *c, apic_particles *p, const Parts &B, int32_t *bs
         int32_t *bs_src = even ? bsA : bsB;
         int32_t *bs_dst = even ? bsB : bsA;
         const bool last = k == nsteps - 1;
-        hipEvent_t *ev = nullptr;
-        if (c->prof_used < c->prof_max && c->prof_step++ % c->prof_every == 0) ev = &c->ev[5 * (size_t)c->prof_used++];
+        hipEvent_t *ev = profile_events(c, false);
         if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[0], s));
         int32_t *tot_k = tot + (even ? 0 : nb), *tot_n = tot + (even ? nb : 0);
         HIPCHK(c, launch_step_count(c->g, c->mixed, src, bs_src, E, k > 0 ? e32 : nullptr, pc, cnt, tot_k, farcnt,
@@ -752,12 +895,9 @@ apic_status step_run(apic_ctx *c, apic_particles *p, const Parts &B, int32_t *bs
     return APIC_OK;
 }
 
-}  // namespace apic_host
-
-extern "C" {
-
-apic_status apic_step(apic_ctx *c, apic_particles *p, void *rho, double *E, float *E32, int nsteps, double *diag,
-                      void *ws, void *stream) {
+// apic_step; ws_pages: ws holds the paged storage too.
+apic_status step_checked(apic_ctx *c, apic_particles *p, void *rho, double *E, float *E32, int nsteps, double *diag,
+                         void *ws, bool ws_pages, hipStream_t s) {
     if (!c) return APIC_EINVAL;
     if (c->g.em) return fail(c, APIC_EUNSUPPORTED, "electromagnetic context: use apic_em_step");
     apic_status st = check_parts(c, p, true);
@@ -765,7 +905,16 @@ apic_status apic_step(apic_ctx *c, apic_particles *p, void *rho, double *E, floa
     if (!E || !ws || nsteps < 0) return fail(c, APIC_EINVAL, "E, workspace and nsteps >= 0 are required");
     if (nsteps == 0) return APIC_OK;
     return step_run(c, p, parts_ws(c, ws), wsp<int32_t>(ws, c->o_bstart), true, rho, E, E32, nsteps, diag, ws,
-                    (hipStream_t)stream);
+                    ws_pages, s);
+}
+
+}  // namespace apic_host
+
+extern "C" {
+
+apic_status apic_step(apic_ctx *c, apic_particles *p, void *rho, double *E, float *E32, int nsteps, double *diag,
+                      void *ws, void *stream) {
+    return step_checked(c, p, rho, E, E32, nsteps, diag, ws, true, (hipStream_t)stream);
 }
 
 apic_status apic_step_pair(apic_ctx *c, apic_particles *p, apic_particles *q, void *rho, double *E, float *E32,
@@ -782,14 +931,16 @@ apic_status apic_step_pair(apic_ctx *c, apic_particles *p, apic_particles *q, vo
         return fail(c, APIC_EINVAL, "the two particle buffers must not share arrays");
     *in_q = nsteps & 1;
     if (nsteps == 0) return APIC_OK;
-    return step_run(c, p, parts_of(q), q->bucket_start, false, rho, E, E32, nsteps, diag, ws, (hipStream_t)stream);
+    return step_run(c, p, parts_of(q), q->bucket_start, false, rho, E, E32, nsteps, diag, ws, true,
+                    (hipStream_t)stream);
 }
 
 apic_status apic_step_static(apic_ctx *c, apic_particles *p, void *rho, double *E, float *E32, int nsteps,
                              double *diag, void *stream) {
     if (!c) return APIC_EINVAL;
-    if (c->ws_bytes > APIC_STATIC_WS_BYTES) {
-        c->err = "apic_step_static: the context needs " + std::to_string(c->ws_bytes) +
+    // (the paged storage is left out where only the reordering step's workspace fits)
+    if (c->ws_step_bytes > APIC_STATIC_WS_BYTES) {
+        c->err = "apic_step_static: the context needs " + std::to_string(c->ws_step_bytes) +
                  " bytes of workspace, above the fixed array's " + std::to_string((size_t)APIC_STATIC_WS_BYTES);
         return APIC_EINVAL;
     }
@@ -799,7 +950,7 @@ apic_status apic_step_static(apic_ctx *c, apic_particles *p, void *rho, double *
                     "are not powers of two up to 1024)");
     void *ws = nullptr;
     HIPCHK(c, scratch_address(&ws));
-    return apic_step(c, p, rho, E, E32, nsteps, diag, ws, stream);
+    return step_checked(c, p, rho, E, E32, nsteps, diag, ws, c->ws_bytes <= APIC_STATIC_WS_BYTES, (hipStream_t)stream);
 }
 
 apic_status apic_profile_enable(apic_ctx *c, int max_steps) {
@@ -810,6 +961,7 @@ apic_status apic_profile_enable(apic_ctx *c, int max_steps) {
     c->prof_step = 0;
     if (max_steps == 0) return APIC_OK;
     c->ev.resize(5 * (size_t)max_steps);
+    c->ev_paged.assign(max_steps, 0);
     for (auto &e : c->ev) HIPCHK(c, hipEventCreate(&e));
     c->prof_max = max_steps;
     return APIC_OK;
@@ -840,6 +992,8 @@ apic_status apic_profile_read(apic_ctx *c, double ms[4], int *steps) {
     HIPCHK(c, hipEventSynchronize(c->ev[5 * (size_t)(c->prof_used - 1) + (c->prof_all ? 4 : 3)]));
     for (int st = 0; st < c->prof_used; ++st) {
         for (int k = c->prof_all ? 0 : 2; k < (c->prof_all ? 4 : 3); ++k) {
+            // a step on paged particles is its push and the field solve
+            if (c->ev_paged[st] && k < 2) continue;
             float t = 0.0f;
             HIPCHK(c, hipEventElapsedTime(&t, c->ev[5 * (size_t)st + k], c->ev[5 * (size_t)st + k + 1]));
             ms[k] += t;

@@ -5,6 +5,7 @@
 
 #include "apic.h"
 #include "apic_internal.h"
+#include "apic_pages.h"
 
 #include <hipfft/hipfft.h>
 
@@ -31,12 +32,20 @@ struct apic_ctx {
     size_t o_e32;     // mixed electrostatic step in 2D and 3D: E between steps, binary32 [dim][G]
     size_t o_cnt, o_offs, o_farcnt, o_farcur, o_tot, o_deep;
     size_t o_keys2, o_idx, o_idx2, o_rcnt, o_roff, o_rpart;
+    // paged storage of calls of several steps (npages = 0: not used by this context);
+    // it shares the front of the workspace with the arrays that only the sort
+    // and the reordering step use
+    int64_t npages = 0;
+    size_t o_pool, o_out, o_ptab, o_pqueue, o_phead, o_praw, o_phole, o_pcode, o_porder, o_pfar, o_plcnt, o_ploff,
+        o_pcnt, o_pds, o_pps;
     size_t ws_bytes;
+    size_t ws_step_bytes;     // the workspace without the paged storage's part beyond the shared front
     double dV, mass;
     // per-phase timing (apic_profile_enable)
     std::vector<hipEvent_t> ev;   // 5 events per profiled step
     int prof_max = 0, prof_used = 0;
     bool prof_all = true;          // events around every phase, or only around the push pass
+    std::vector<char> ev_paged;    // whether a profiled step kept the particles in place (no count pass)
     int prof_every = 1;            // events on one step in prof_every
     int64_t prof_step = 0;         // steps seen since profiling was armed
 };
@@ -81,6 +90,16 @@ int64_t max_per_bucket(const apic_ctx *c);
 apic_status field_from_acc(apic_ctx *c, void *acc, bool acc_is_rho, double *E, float *E32, double *diag,
                            double *we, double *charge, int npush, int clear, void *ws, hipStream_t s,
                            const int32_t *nlive = nullptr);
+// Calls of at least this many steps keep the particles in pages between the
+// steps: what a step saves then pays for the copy at the call's end.
+constexpr int kPagedSteps = 8;
+
+// Paged storage of a call's step k in the workspace ws, and the launches that start a call: acc (nacc 64-bit words) is
+// what the first push adds to.
+apic::PageStep page_step(const apic_ctx *c, void *ws, int k);
+apic_status page_begin(apic_ctx *c, const int32_t *bstart, void *acc, int64_t nacc, void *ws, hipStream_t s);
+// Events of the step about to run (NULL: not profiled); paged: it keeps the particles in place.
+hipEvent_t *profile_events(apic_ctx *c, bool paged);
 apic_status copy_parts(apic_ctx *c, const Parts &dst, const Parts &src, hipStream_t s);
 
 }  // namespace apic_host

@@ -360,6 +360,37 @@ apic_status apic_em_gather_push(apic_ctx *c, apic_particles *p, const double *F,
     return APIC_OK;
 }
 
+// apic_em_step on paged particles (apic_pages.hip).
+static apic_status em_step_paged(apic_ctx *c, apic_particles *p, double *F, double *J, int nsteps, double *diag,
+                                 void *ws, hipStream_t s) {
+    const int nb = c->g.nbuckets;
+    const int64_t G = (int64_t)c->d.nx * c->d.ny;
+    double *jacc = wsp<double>(ws, c->o_jacc), *F2 = wsp<double>(ws, c->o_f2);
+    const Parts A = parts_of(p);
+    const PushC pc = push_coeffs(c, 1.0, 1);
+    const double c2 = c->d.c_light * c->d.c_light;
+    const apic_status st = page_begin(c, p->bucket_start, jacc, 2 * 3 * G, ws, s);
+    if (st != APIC_OK) return st;
+    for (int k = 0; k < nsteps; ++k) {
+        const apic::PageStep t = page_step(c, ws, k);
+        const bool even = (k & 1) == 0, last = k == nsteps - 1;
+        double *Fk = even ? F : F2, *Fk1 = even ? F2 : F;
+        double *Jk = jacc + (even ? 0 : 3 * G), *Jk1 = jacc + (even ? 3 * G : 0);
+        hipEvent_t *ev = profile_events(c, true);
+        if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
+        HIPCHK(c, launch_page_push(c->g, c->mixed, t, k == 0 ? &A : nullptr, p->bucket_start, c->n, max_per_bucket(c),
+                                   Fk, nullptr, pc, Jk, diag ? c->dev.part_push : nullptr, c->dev, s));
+        if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
+        HIPCHK(c, launch_fdtd_step(c->g, Fk, Fk1, Jk, Jk1, (J && last) ? J : nullptr, c->d.dt, c2, c->d.bz, c->dV,
+                                   c->mass, nb, diag, c->dev, s));
+        if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[4], s));
+    }
+    HIPCHK(c, launch_page_end(c->g, c->mixed, page_step(c, ws, nsteps), c->n, max_per_bucket(c), A, p->bucket_start,
+                              c->dev, s));
+    if (nsteps & 1) HIPCHK(c, launch_copy_bytes(F, F2, 48 * G, s));
+    return APIC_OK;
+}
+
 apic_status apic_em_step(apic_ctx *c, apic_particles *p, double *F, double *J, int nsteps, double *diag, void *ws,
                          void *stream) {
     apic_status st = check_em(c);
@@ -377,6 +408,7 @@ apic_status apic_em_step(apic_ctx *c, apic_particles *p, double *F, double *J, i
     int32_t *tot = wsp<int32_t>(ws, c->o_tot);
     int32_t *deep = wsp<int32_t>(ws, c->o_deep);
     double *jacc = wsp<double>(ws, c->o_jacc);
+    if (nsteps >= kPagedSteps && c->npages && !p->perm) return em_step_paged(c, p, F, J, nsteps, diag, ws, s);
     Parts A = parts_of(p), B = parts_ws(c, ws);
     int32_t *bsA = p->bucket_start, *bsB = wsp<int32_t>(ws, c->o_bstart);
     const PushC pc = push_coeffs(c, 1.0, 1);
@@ -395,8 +427,7 @@ apic_status apic_em_step(apic_ctx *c, apic_particles *p, double *F, double *J, i
         int32_t *bs_src = even ? bsA : bsB;
         int32_t *bs_dst = even ? bsB : bsA;
         const bool last = k == nsteps - 1;
-        hipEvent_t *ev = nullptr;
-        if (c->prof_used < c->prof_max && c->prof_step++ % c->prof_every == 0) ev = &c->ev[5 * (size_t)c->prof_used++];
+        hipEvent_t *ev = profile_events(c, false);
         if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[0], s));
         int32_t *tot_k = tot + (even ? 0 : nb), *tot_n = tot + (even ? nb : 0);
         // F^n in F on even steps and in F2 on odd ones; J^{n+1/2} alternates likewise
