@@ -178,13 +178,9 @@ void layout(apic_ctx *c) {
     c->o_vx = take(r * n);
     if (vdim >= 2) c->o_vy = take(r * n);
     if (vdim >= 3) c->o_vz = take(r * n);
-    c->o_keys = take(4 * n);
-    c->o_keys2 = take(4 * n);
     c->o_idx = take(4 * n);
-    c->o_idx2 = take(4 * n);
-    c->o_rcnt = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
-    c->o_roff = take(4 * (int64_t)sort_chunks(n) * sort_table_entries());
-    c->o_rpart = take(4 * (int64_t)sort_part_entries());
+    c->o_rcnt = take(4 * sort_tallies(n, (int)nb));
+    c->o_rpart = take(4 * sort_groups(n, (int)nb));
     c->ws_step_bytes = c->ws_bytes = off;
     c->npages = pages_wanted(c);
     if (!c->npages) return;
@@ -722,24 +718,10 @@ apic_status apic_sort_by_cell(apic_ctx *c, apic_particles *p, void *ws, void *st
     if (st != APIC_OK) return st;
     if (!ws) return fail(c, APIC_EINVAL, "workspace is NULL");
     hipStream_t s = (hipStream_t)stream;
-    const int nb = c->g.nbuckets;
-    int32_t *k0 = wsp<int32_t>(ws, c->o_keys), *k1 = wsp<int32_t>(ws, c->o_keys2);
-    int32_t *i0 = wsp<int32_t>(ws, c->o_idx), *i1 = wsp<int32_t>(ws, c->o_idx2);
-    Parts src = parts_of(p), tmp = parts_ws(c, ws);
-    // stable order by key
-    HIPCHK(c, launch_keys_init(c->g, c->mixed, src, c->n, k0, i0, c->dev, s));
-    int bits = 1;
-    while ((1ll << bits) < (int64_t)nb) ++bits;
-    for (int shift = 0; shift < bits; shift += 8) {
-        HIPCHK(c, launch_radix_pass(k0, i0, k1, i1, c->n, shift, wsp<int32_t>(ws, c->o_rcnt),
-                                    wsp<int32_t>(ws, c->o_roff), wsp<int32_t>(ws, c->o_rpart), c->dev, s));
-        std::swap(k0, k1);
-        std::swap(i0, i1);
-    }
-    // bucket table from the sorted keys
-    HIPCHK(c, launch_bucket_table(k0, c->n, nb, p->bucket_start, max_per_bucket(c), c->dev, s));
-    HIPCHK(c, launch_gather_parts(c->g, c->mixed, src, tmp, c->n, i0, p->perm, c->dev, s));
-    return copy_parts(c, src, tmp, s);
+    HIPCHK(c, launch_sort(c->g, c->mixed, parts_of(p), parts_ws(c, ws), c->n, p->perm, wsp<int32_t>(ws, c->o_idx),
+                          wsp<int32_t>(ws, c->o_rcnt), wsp<int32_t>(ws, c->o_rpart), p->bucket_start,
+                          max_per_bucket(c), c->dev, s));
+    return APIC_OK;
 }
 
 apic_status apic_deposit(apic_ctx *c, const apic_particles *p, void *rho, void *stream) {

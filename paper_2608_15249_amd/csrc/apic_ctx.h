@@ -26,12 +26,12 @@ struct apic_ctx {
     std::string err;
     // workspace layout (byte offsets)
     size_t o_x, o_y, o_z, o_cell, o_ox, o_oy, o_oz, o_vx, o_vy, o_vz;
-    size_t o_keys, o_bstart, o_acc, o_rho, o_rhat, o_ehat;
+    size_t o_bstart, o_acc, o_rho, o_rhat, o_ehat;
     size_t o_jacc;    // electromagnetic step: J [2][3][G] (two buffers)
     size_t o_f2;      // electromagnetic step: the second field buffer [6][G]
     size_t o_e32;     // mixed electrostatic step in 2D and 3D: E between steps, binary32 [dim][G]
     size_t o_cnt, o_offs, o_farcnt, o_farcur, o_tot, o_deep;
-    size_t o_keys2, o_idx, o_idx2, o_rcnt, o_roff, o_rpart;
+    size_t o_idx, o_rcnt, o_rpart;
     // paged storage of calls of several steps (npages = 0: not used by this context);
     // it shares the front of the workspace with the arrays that only the sort
     // and the reordering step use

@@ -121,21 +121,15 @@ hipError_t launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_set_step(int *step, int v, hipStream_t s);
 hipError_t launch_copy_bytes(void *dst, const void *src, int64_t bytes, hipStream_t s);
 
-// general sort (arbitrary input order): stable LSD radix sort of
-// (bucket key, index), the bucket table of the sorted keys, then a gather of
-// the arrays
-hipError_t launch_keys_init(const Geo &g, bool mixed, const Parts &p, int64_t n, int32_t *keys,
-                            int32_t *idx, const CtxDev &c, hipStream_t s);
-int sort_chunks(int64_t n);
-int sort_table_entries();
-int sort_part_entries();
-hipError_t launch_radix_pass(const int32_t *kin, const int32_t *iin, int32_t *kout, int32_t *iout,
-                             int64_t n, int shift, int32_t *cnt, int32_t *off, int32_t *part,
-                             const CtxDev &c, hipStream_t s);
-hipError_t launch_bucket_table(const int32_t *sorted_keys, int64_t n, int nb, int32_t *start,
-                               int64_t max_per_bucket, const CtxDev &c, hipStream_t s);
-hipError_t launch_gather_parts(const Geo &g, bool mixed, const Parts &src, const Parts &dst, int64_t n,
-                               const int32_t *idx, int32_t *perm, const CtxDev &c, hipStream_t s);
+// general sort (arbitrary input order, apic_sort.hip): stable radix passes over
+// the particle arrays p by bucket (tmp: a second buffer set), and the bucket
+// table. perm (may be NULL): input index of each sorted particle, with idx [n]
+// as scratch. cnt [sort_tallies] and part [sort_groups]: scratch.
+int64_t sort_tallies(int64_t n, int nb);
+int64_t sort_groups(int64_t n, int nb);
+hipError_t launch_sort(const Geo &g, bool mixed, const Parts &p, const Parts &tmp, int64_t n, int32_t *perm,
+                       int32_t *idx, int32_t *cnt, int32_t *part, int32_t *start, int64_t max_per_bucket,
+                       const CtxDev &c, hipStream_t s);
 
 // deposit of current positions into acc (double weights or int64 sums)
 hipError_t launch_deposit(const Geo &g, bool mixed, const Parts &p, int64_t n, const int32_t *bstart,

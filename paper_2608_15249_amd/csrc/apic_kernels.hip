@@ -131,206 +131,6 @@ __global__ void __launch_bounds__(1024) k_scan_tot(int32_t *tot, int32_t *start,
     }
 }
 
-// ---- general sort: stable LSD radix sort of (bucket key, index) ----------------
-// Keys are bucket indices; each pass orders by 8 more key bits, keeping the
-// previous order among equal digits (stable), so the result is the stable
-// counting sort of the input by bucket. Per pass: tallies per (chunk, wave,
-// digit), one exclusive scan in (digit, chunk, wave) order, and a scatter that
-// hands out slots per (wave, digit) in the order the wave meets its elements
-// (lanes with equal digits are ranked with ballots). Each wave owns a
-// contiguous range of its chunk, so (chunk, wave, element) order is input
-// order and every pass is stable; no atomic decides an element's slot.
-constexpr int kRadixBits = 8;
-constexpr int kRadix = 1 << kRadixBits;
-constexpr int kSortPer = 16;                    // elements per thread and chunk
-constexpr int kSortChunk = kBlock * kSortPer;   // elements per chunk (block)
-constexpr int kSortTab = kWaves * kRadix;       // tallies per chunk
-
-template <bool MIX, int DIM, int VDIM>
-__global__ void __launch_bounds__(kBlock) k_keys_init(Geo g, Parts p, int64_t n, int32_t *keys, int32_t *idx,
-                                                      CtxDev c) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        Pt<MIX> q;
-        bool ok = load_pt<MIX, DIM, VDIM>(p, i, g, q);
-        if (g.walls && q.ix >= g.nxp) {
-            // outside the box between the walls
-            ok = false;
-            q.ix = 0;
-        }
-        if (!ok) raise_err(c.err, ERR_DOMAIN);
-        keys[i] = bucket_of<MIX, DIM>(g, q.ix, q.iy, q.iz);
-        idx[i] = (int32_t)i;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_count(const int32_t *keys, int64_t n, int shift, int32_t *cnt) {
-    __shared__ int32_t s[kSortTab];
-    for (int t = threadIdx.x; t < kSortTab; t += blockDim.x) s[t] = 0;
-    __syncthreads();
-    const int w = threadIdx.x >> 6;
-    // wave w owns the contiguous range [w*64*kSortPer, (w+1)*64*kSortPer) of the chunk
-    const int64_t base = (int64_t)blockIdx.x * kSortChunk + (int64_t)w * 64 * kSortPer + __lane_id();
-    for (int j = 0; j < kSortPer; ++j) {
-        const int64_t i = base + j * 64;
-        if (i < n) atomicAdd(&s[w * kRadix + ((keys[i] >> shift) & (kRadix - 1))], 1);
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < kSortTab; t += blockDim.x) cnt[(int64_t)blockIdx.x * kSortTab + t] = s[t];
-}
-
-// Exclusive scan of the tallies in (digit, chunk, wave) order, in three
-// launches that read the tally table row by row (thread d of a workgroup
-// handles digit d, so every load and store is coalesced): per range of R
-// chunks the digit totals, then (one workgroup) the first slot of every
-// digit in every range, then the offsets inside each range.
-static_assert(kRadix == kBlock, "one thread per digit");
-constexpr int kRadixParts = 256;  // chunk ranges at most
-
-__device__ __forceinline__ void chunk_range(int nchunks, int R, int &c0, int &c1) {
-    c0 = (int)blockIdx.x * R;
-    c1 = min(c0 + R, nchunks);
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_part(const int32_t *cnt, int nchunks, int R, int32_t *part) {
-    const int d = threadIdx.x;
-    int c0, c1;
-    chunk_range(nchunks, R, c0, c1);
-    int32_t s = 0;
-    for (int ch = c0; ch < c1; ++ch) {
-        const int32_t *row = cnt + (int64_t)ch * kSortTab + d;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) s += row[w * kRadix];
-    }
-    part[blockIdx.x * kRadix + d] = s;
-}
-
-// part[r][d] (digit d's tally in range r) becomes the slot where range r's
-// elements of digit d start: sum of all lower digits plus digit d in ranges
-// before r.
-__global__ void __launch_bounds__(kBlock) k_radix_base(int32_t *part, int P) {
-    __shared__ int32_t sw[kWaves];
-    const int d = threadIdx.x, lane = d & 63, w = d >> 6;
-    int32_t tot = 0;
-#pragma unroll 16
-    for (int r = 0; r < P; ++r) tot += part[r * kRadix + d];
-    int32_t inc = tot;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t y = __shfl_up(inc, o);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) sw[w] = inc;
-    __syncthreads();
-    int32_t run = inc - tot;
-    for (int i = 0; i < w; ++i) run += sw[i];
-#pragma unroll 16
-    for (int r = 0; r < P; ++r) {
-        const int32_t t = part[r * kRadix + d];
-        part[r * kRadix + d] = run;
-        run += t;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_off(const int32_t *cnt, const int32_t *part, int nchunks, int R,
-                                                      int32_t *off) {
-    const int d = threadIdx.x;
-    int c0, c1;
-    chunk_range(nchunks, R, c0, c1);
-    int32_t run = part[blockIdx.x * kRadix + d];
-    for (int ch = c0; ch < c1; ++ch) {
-        const int64_t a = (int64_t)ch * kSortTab + d;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const int32_t t = cnt[a + w * kRadix];
-            off[a + w * kRadix] = run;
-            run += t;
-        }
-    }
-}
-
-// Bucket table of the sorted keys: start[b] is the first position whose key
-// is at least b (start[nb] = n). Position i (0 <= i <= n) writes the entries of
-// the buckets in (key[i-1], key[i]], with key[-1] = -1 and key[n] = nb, so each
-// entry has exactly one writer; the clamp keeps keys of out-of-domain
-// particles (already reported) inside the table.
-__global__ void k_bucket_bounds(const int32_t *key, int64_t n, int nb, int32_t *start) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int lo = max(i == 0 ? 0 : key[i - 1] + 1, 0);
-        const int hi = min(i == n ? nb : key[i], nb);
-        for (int b = lo; b <= hi; ++b) start[b] = (int32_t)i;
-    }
-}
-
-// Buckets holding more particles than the fixed-point node sums allow.
-__global__ void k_bucket_check(const int32_t *start, int nb, int64_t max_per, CtxDev c) {
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += gridDim.x * blockDim.x)
-        if ((int64_t)start[b + 1] - start[b] > max_per) raise_err(c.err, ERR_OVERFLOW);
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_scatter(const int32_t *kin, const int32_t *iin, int32_t *kout,
-                                                          int32_t *iout, int64_t n, int shift, const int32_t *off,
-                                                          CtxDev c) {
-    __shared__ int32_t sRun[kSortTab];
-    for (int t = threadIdx.x; t < kSortTab; t += blockDim.x) sRun[t] = off[(int64_t)blockIdx.x * kSortTab + t];
-    __syncthreads();
-    const int w = threadIdx.x >> 6;
-    const uint64_t lt = lanemask_lt();
-    // same element -> wave mapping as k_radix_count; wave-major order is input order (stable)
-    const int64_t base = (int64_t)blockIdx.x * kSortChunk + (int64_t)w * 64 * kSortPer + __lane_id();
-    for (int j = 0; j < kSortPer; ++j) {
-        const int64_t i = base + j * 64;
-        const bool act = i < n;
-        const int key = act ? kin[i] : 0;
-        const int d = (key >> shift) & (kRadix - 1);
-        // lanes holding the same digit
-        uint64_t peers = __ballot(act);
-#pragma unroll
-        for (int bit = 0; bit < kRadixBits; ++bit) {
-            const uint64_t bb = __ballot(act && ((d >> bit) & 1));
-            peers &= ((d >> bit) & 1) ? bb : ~bb;
-        }
-        if (act) {
-            const int basek = sRun[w * kRadix + d];
-            const int slot = basek + (int)__popcll(peers & lt);
-            if ((int)__lane_id() == __ffsll((unsigned long long)peers) - 1)
-                sRun[w * kRadix + d] = basek + (int)__popcll(peers);
-            if (slot >= 0 && slot < n) {
-                kout[slot] = key;
-                iout[slot] = iin[i];
-            } else {
-                raise_err(c.err, ERR_ORDER);
-            }
-        }
-    }
-}
-
-// dst[j] = src[idx[j]] for every particle array; perm (optional) = idx.
-template <bool MIX, int DIM, int VDIM>
-__global__ void __launch_bounds__(kBlock) k_gather_parts(Parts src, Parts dst, int64_t n, const int32_t *idx,
-                                                         int32_t *perm, CtxDev c) {
-    using R = typename Pt<MIX>::R;
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = idx[j];
-        if (i < 0 || i >= n) {
-            raise_err(c.err, ERR_ORDER);
-            continue;
-        }
-        if constexpr (MIX) {
-            dst.cell[j] = src.cell[i];
-            dst.ox[j] = src.ox[i];
-            if constexpr (DIM >= 2) dst.oy[j] = src.oy[i];
-            if constexpr (DIM == 3) dst.oz[j] = src.oz[i];
-        } else {
-            dst.x[j] = src.x[i];
-            if constexpr (DIM >= 2) dst.y[j] = src.y[i];
-            if constexpr (DIM == 3) dst.z[j] = src.z[i];
-        }
-        ((R *)dst.vx)[j] = ((const R *)src.vx)[i];
-        if constexpr (VDIM >= 2) ((R *)dst.vy)[j] = ((const R *)src.vy)[i];
-        if constexpr (VDIM >= 3) ((R *)dst.vz)[j] = ((const R *)src.vz)[i];
-        if (perm) perm[j] = (int32_t)i;
-    }
-}
-
 // ---- deposit of current positions ---------------------------------------------
 template <bool MIX, int DIM, int VDIM>
 __global__ void __launch_bounds__(kBlock) k_deposit_direct(Geo g, Parts p, int64_t n,
@@ -1523,48 +1323,6 @@ hipError_t launch_copy_bytes(void *dst, const void *src, int64_t bytes, hipStrea
     return hipGetLastError();
 }
 
-
-hipError_t launch_keys_init(const Geo &g, bool mixed, const Parts &p, int64_t n, int32_t *keys, int32_t *idx,
-                            const CtxDev &c, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    APIC_DISPATCH(g, mixed,
-                  hipLaunchKernelGGL((k_keys_init<MIX, DIM, VDIM>), dim3(blocks_for(n)), dim3(kBlock), 0, s, g, p, n,
-                                     keys, idx, c));
-    return hipGetLastError();
-}
-
-int sort_chunks(int64_t n) { return (int)((n + kSortChunk - 1) / kSortChunk); }
-int sort_table_entries() { return kSortTab; }
-int sort_part_entries() { return kRadixParts * kRadix; }
-
-hipError_t launch_bucket_table(const int32_t *sorted_keys, int64_t n, int nb, int32_t *start, int64_t max_per_bucket,
-                               const CtxDev &c, hipStream_t s) {
-    hipLaunchKernelGGL(k_bucket_bounds, dim3(blocks_for(n + 1)), dim3(kBlock), 0, s, sorted_keys, n, nb, start);
-    hipLaunchKernelGGL(k_bucket_check, dim3(blocks_for(nb)), dim3(kBlock), 0, s, start, nb, max_per_bucket, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_radix_pass(const int32_t *kin, const int32_t *iin, int32_t *kout, int32_t *iout, int64_t n,
-                             int shift, int32_t *cnt, int32_t *off, int32_t *part, const CtxDev &c, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int C = sort_chunks(n);
-    hipLaunchKernelGGL(k_radix_count, dim3(C), dim3(kBlock), 0, s, kin, n, shift, cnt);
-    const int R = (C + kRadixParts - 1) / kRadixParts, P = (C + R - 1) / R;
-    hipLaunchKernelGGL(k_radix_part, dim3(P), dim3(kBlock), 0, s, cnt, C, R, part);
-    hipLaunchKernelGGL(k_radix_base, dim3(1), dim3(kBlock), 0, s, part, P);
-    hipLaunchKernelGGL(k_radix_off, dim3(P), dim3(kBlock), 0, s, cnt, part, C, R, off);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(C), dim3(kBlock), 0, s, kin, iin, kout, iout, n, shift, off, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_parts(const Geo &g, bool mixed, const Parts &src, const Parts &dst, int64_t n,
-                               const int32_t *idx, int32_t *perm, const CtxDev &c, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    APIC_DISPATCH(g, mixed,
-                  hipLaunchKernelGGL((k_gather_parts<MIX, DIM, VDIM>), dim3(blocks_for(n)), dim3(kBlock), 0, s, src,
-                                     dst, n, idx, perm, c));
-    return hipGetLastError();
-}
 
 hipError_t launch_deposit(const Geo &g, bool mixed, const Parts &p, int64_t n, const int32_t *bstart, void *acc,
                           const CtxDev &c, hipStream_t s) {
