@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(kBlock) k_em_gather_push(Geo g, Parts p, int64
             if (pc.move) ok = move_pt<MIX, 2>(q, g, pc, sx, sy, sz) && ok;
         }
         if (!ok) bad = 1;
-        store_pt<MIX, 2, 3>(p, i, q);
+        store_moved<MIX, 2, 3>(p, i, q, pc.move != 0);
     }
     if (bad) raise_err(c.err, ERR_DOMAIN);
 }

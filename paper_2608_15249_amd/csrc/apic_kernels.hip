@@ -151,6 +151,10 @@ __global__ void __launch_bounds__(kBlock) k_deposit_direct(Geo g, Parts p, int64
     }
 }
 
+// Tiled forms of the deposit and of the gather + push: one workgroup per
+// bucket, kAhead particles per thread loaded before the first is used.
+constexpr int kAhead = 4;
+
 template <bool MIX, int DIM, int VDIM>
 __global__ void __launch_bounds__(kBlock) k_deposit_tiled(Geo g, Parts p, const int32_t *bstart,
                                                           typename AccOf<MIX>::T *acc, CtxDev c) {
@@ -168,41 +172,48 @@ __global__ void __launch_bounds__(kBlock) k_deposit_tiled(Geo g, Parts p, const 
     for (int t = threadIdx.x; t < wx * wy * wz; t += blockDim.x) sA[t] = (A)0;
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        Pt<MIX> q;
-        if (!load_pt<MIX, DIM, VDIM>(p, i, g, q)) {
-            raise_err(c.err, ERR_DOMAIN);
-            continue;
-        }
-        A w[8];
-        dep_weights<MIX, DIM>(q, g, w);
-        int lx = q.ix - x0;
-        int ly = (DIM >= 2) ? q.iy - y0 : 0;
-        int lz = (DIM == 3) ? q.iz - z0 : 0;
-        bool inl = (lx >= 0) && (lx <= wx - 2);
-        if constexpr (DIM >= 2) inl = inl && ly >= 0 && ly <= wy - 2;
-        if constexpr (DIM == 3) inl = inl && lz >= 0 && lz <= wz - 2;
-        if (inl) {
-            int a = (lz * wy + ly) * wx + lx;
-            acc_add_lds<MIX>(&sA[a], w[0]);
-            acc_add_lds<MIX>(&sA[a + 1], w[1]);
-            if constexpr (DIM >= 2) {
-                acc_add_lds<MIX>(&sA[a + wx], w[2]);
-                acc_add_lds<MIX>(&sA[a + wx + 1], w[3]);
+    for (int base = i0 + threadIdx.x; base < i1; base += kAhead * blockDim.x) {
+        Raw<MIX> r[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, 0>(p, min(base + j * (int)blockDim.x, i1 - 1), r[j]);
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            if (base + j * (int)blockDim.x >= i1) break;
+            Pt<MIX> q;
+            if (!decode<MIX, DIM, 0>(r[j], g, q)) {
+                raise_err(c.err, ERR_DOMAIN);
+                continue;
             }
-            if constexpr (DIM == 3) {
-                const int wxy = wx * wy;
-                acc_add_lds<MIX>(&sA[a + wxy], w[4]);
-                acc_add_lds<MIX>(&sA[a + wxy + 1], w[5]);
-                acc_add_lds<MIX>(&sA[a + wxy + wx], w[6]);
-                acc_add_lds<MIX>(&sA[a + wxy + wx + 1], w[7]);
+            A w[8];
+            dep_weights<MIX, DIM>(q, g, w);
+            int lx = q.ix - x0;
+            int ly = (DIM >= 2) ? q.iy - y0 : 0;
+            int lz = (DIM == 3) ? q.iz - z0 : 0;
+            bool inl = (lx >= 0) && (lx <= wx - 2);
+            if constexpr (DIM >= 2) inl = inl && ly >= 0 && ly <= wy - 2;
+            if constexpr (DIM == 3) inl = inl && lz >= 0 && lz <= wz - 2;
+            if (inl) {
+                int a = (lz * wy + ly) * wx + lx;
+                acc_add_lds<MIX>(&sA[a], w[0]);
+                acc_add_lds<MIX>(&sA[a + 1], w[1]);
+                if constexpr (DIM >= 2) {
+                    acc_add_lds<MIX>(&sA[a + wx], w[2]);
+                    acc_add_lds<MIX>(&sA[a + wx + 1], w[3]);
+                }
+                if constexpr (DIM == 3) {
+                    const int wxy = wx * wy;
+                    acc_add_lds<MIX>(&sA[a + wxy], w[4]);
+                    acc_add_lds<MIX>(&sA[a + wxy + 1], w[5]);
+                    acc_add_lds<MIX>(&sA[a + wxy + wx], w[6]);
+                    acc_add_lds<MIX>(&sA[a + wxy + wx + 1], w[7]);
+                }
+            } else {
+                raise_err(c.err, ERR_ORDER);
+                if constexpr (DIM == 3)
+                    deposit_global3<MIX>(acc, g, q.ix, q.iy, q.iz, w);
+                else
+                    deposit_global<MIX, DIM>(acc, g, q.ix, q.iy, w);
             }
-        } else {
-            raise_err(c.err, ERR_ORDER);
-            if constexpr (DIM == 3)
-                deposit_global3<MIX>(acc, g, q.ix, q.iy, q.iz, w);
-            else
-                deposit_global<MIX, DIM>(acc, g, q.ix, q.iy, w);
         }
     }
     __syncthreads();
@@ -233,7 +244,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_direct(Geo g, Parts p, i
         int sx, sy, sz;
         if (!push_move<MIX, DIM, VDIM, HC>(q, g, pc, ex, ey, ez, pc.move != 0, sx, sy, sz))
             raise_err(c.err, ERR_DOMAIN);
-        store_pt<MIX, DIM, VDIM>(p, i, q);
+        store_moved<MIX, DIM, VDIM>(p, i, q, pc.move != 0);
     }
 }
 
@@ -257,37 +268,45 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, co
         load_e_tile<R, R, DIM>(sE, E, g, x0, y0, ex_w, ey_w);
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        Pt<MIX> q;
-        if (!load_pt<MIX, DIM, VDIM>(p, i, g, q)) {
-            raise_err(c.err, ERR_DOMAIN);
-            continue;
-        }
-        const int lx = q.ix - x0, ly = (DIM >= 2) ? q.iy - y0 : 0, lz = (DIM == 3) ? q.iz - z0 : 0;
-        bool inl = lx >= 0 && lx < ex_w - 1;
-        if constexpr (DIM >= 2) inl = inl && ly >= 0 && ly < ey_w - 1;
-        if constexpr (DIM == 3) inl = inl && lz >= 0 && lz < ez_w - 1;
-        R ex, ey, ez = R(0);
-        if constexpr (DIM == 3) {
-            if (inl) {
-                const int wxy = ex_w * ey_w;
-                gather_lds3<R>(sE, ex_w, wxy, wxy * ez_w, lx, ly, lz, q.fx, q.fy, q.fz, ex, ey, ez);
-            } else {
-                raise_err(c.err, ERR_ORDER);
-                gather_global3<R, R>(E, g, q.ix, q.iy, q.iz, q.fx, q.fy, q.fz, ex, ey, ez);
+    for (int base = i0 + threadIdx.x; base < i1; base += kAhead * blockDim.x) {
+        Raw<MIX> r[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, VDIM>(p, min(base + j * (int)blockDim.x, i1 - 1), r[j]);
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const int i = base + j * (int)blockDim.x;
+            if (i >= i1) break;
+            Pt<MIX> q;
+            if (!decode<MIX, DIM, VDIM>(r[j], g, q)) {
+                raise_err(c.err, ERR_DOMAIN);
+                continue;
             }
-        } else {
-            if (inl) {
-                gather_lds<R, DIM>(sE, ex_w, ex_w * ey_w, lx, ly, q.fx, q.fy, ex, ey);
+            const int lx = q.ix - x0, ly = (DIM >= 2) ? q.iy - y0 : 0, lz = (DIM == 3) ? q.iz - z0 : 0;
+            bool inl = lx >= 0 && lx < ex_w - 1;
+            if constexpr (DIM >= 2) inl = inl && ly >= 0 && ly < ey_w - 1;
+            if constexpr (DIM == 3) inl = inl && lz >= 0 && lz < ez_w - 1;
+            R ex, ey, ez = R(0);
+            if constexpr (DIM == 3) {
+                if (inl) {
+                    const int wxy = ex_w * ey_w;
+                    gather_lds3<R>(sE, ex_w, wxy, wxy * ez_w, lx, ly, lz, q.fx, q.fy, q.fz, ex, ey, ez);
+                } else {
+                    raise_err(c.err, ERR_ORDER);
+                    gather_global3<R, R>(E, g, q.ix, q.iy, q.iz, q.fx, q.fy, q.fz, ex, ey, ez);
+                }
             } else {
-                raise_err(c.err, ERR_ORDER);
-                gather_global<R, R, DIM>(E, g, q.ix, q.iy, q.fx, q.fy, ex, ey);
+                if (inl) {
+                    gather_lds<R, DIM>(sE, ex_w, ex_w * ey_w, lx, ly, q.fx, q.fy, ex, ey);
+                } else {
+                    raise_err(c.err, ERR_ORDER);
+                    gather_global<R, R, DIM>(E, g, q.ix, q.iy, q.fx, q.fy, ex, ey);
+                }
             }
+            int sx, sy, sz;
+            if (!push_move<MIX, DIM, VDIM, HC>(q, g, pc, ex, ey, ez, pc.move != 0, sx, sy, sz))
+                raise_err(c.err, ERR_DOMAIN);
+            store_moved<MIX, DIM, VDIM>(p, i, q, pc.move != 0);
         }
-        int sx, sy, sz;
-        if (!push_move<MIX, DIM, VDIM, HC>(q, g, pc, ex, ey, ez, pc.move != 0, sx, sy, sz))
-            raise_err(c.err, ERR_DOMAIN);
-        store_pt<MIX, DIM, VDIM>(p, i, q);
     }
 }
 

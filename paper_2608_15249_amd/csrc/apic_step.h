@@ -256,14 +256,14 @@ __device__ __forceinline__ void load_raw(const Parts &s, int i, Raw<MIX> &r) {
         r.ox = __builtin_nontemporal_load(&s.ox[i]);
         r.oy = (DIM >= 2) ? __builtin_nontemporal_load(&s.oy[i]) : 0.0f;
         r.oz = (DIM == 3) ? __builtin_nontemporal_load(&s.oz[i]) : 0.0f;
-        r.vx = __builtin_nontemporal_load(&((const float *)s.vx)[i]);
+        r.vx = (VDIM >= 1) ? __builtin_nontemporal_load(&((const float *)s.vx)[i]) : 0.0f;
         r.vy = (VDIM >= 2) ? __builtin_nontemporal_load(&((const float *)s.vy)[i]) : 0.0f;
         r.vz = (VDIM >= 3) ? __builtin_nontemporal_load(&((const float *)s.vz)[i]) : 0.0f;
     } else {
         r.x = s.x[i];
         r.y = (DIM >= 2) ? s.y[i] : 0.0;
         r.z = (DIM == 3) ? s.z[i] : 0.0;
-        r.vx = ((const double *)s.vx)[i];
+        r.vx = (VDIM >= 1) ? ((const double *)s.vx)[i] : 0.0;
         r.vy = (VDIM >= 2) ? ((const double *)s.vy)[i] : 0.0;
         r.vz = (VDIM >= 3) ? ((const double *)s.vz)[i] : 0.0;
     }
