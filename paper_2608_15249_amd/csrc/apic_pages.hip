@@ -277,6 +277,29 @@ __device__ __forceinline__ Raw<MIX> out_get(const PageStep &t, int e) {
     return r;
 }
 
+// One particle from the caller's arrays (through the caches: a bucket starts
+// mid-line, and neighbouring waves share lines).
+template <bool MIX, int DIM, int VDIM>
+__device__ __forceinline__ void read_array(const Parts &s, int i, Raw<MIX> &r) {
+    r = Raw<MIX>{};
+    if constexpr (MIX) {
+        r.c = s.cell[i];
+        r.ox = s.ox[i];
+        if constexpr (DIM >= 2) r.oy = s.oy[i];
+        if constexpr (DIM == 3) r.oz = s.oz[i];
+        r.vx = ((const float *)s.vx)[i];
+        if constexpr (VDIM >= 2) r.vy = ((const float *)s.vy)[i];
+        if constexpr (VDIM >= 3) r.vz = ((const float *)s.vz)[i];
+    } else {
+        r.x = s.x[i];
+        if constexpr (DIM >= 2) r.y = s.y[i];
+        if constexpr (DIM == 3) r.z = s.z[i];
+        r.vx = ((const double *)s.vx)[i];
+        if constexpr (VDIM >= 2) r.vy = ((const double *)s.vy)[i];
+        if constexpr (VDIM >= 3) r.vz = ((const double *)s.vz)[i];
+    }
+}
+
 // One particle to the caller's arrays.
 template <bool MIX, int DIM, int VDIM>
 __device__ __forceinline__ void store_raw(const Parts &s, int i, const Raw<MIX> &r) {
@@ -740,7 +763,7 @@ __global__ void __launch_bounds__(kPagePushMax, 4) k_page_push(Geo g, PageStep t
             if constexpr (FIRST) {
 #pragma unroll
                 for (int j = 0; j < U; ++j)
-                    load_raw<MIX, DIM, VDIM>(src, i0 + min((w + i * nw) * kPage + j * 64 + lane, count - 1), r[j]);
+                    read_array<MIX, DIM, VDIM>(src, i0 + min((w + i * nw) * kPage + j * 64 + lane, count - 1), r[j]);
             } else {
 #pragma unroll
                 for (int j = 0; j < U; ++j) load_slot<MIX, DIM, VDIM>(s, j * 64 + lane, r[j]);
@@ -1142,19 +1165,22 @@ __global__ void __launch_bounds__(kBlock) k_page_end(Geo g, PageStep t, int64_t 
             bstart[b] = dsb;
             if (b == nb - 1) bstart[nb] = dsb + count;
         }
-        // four particles per thread and round, their loads issued before the first store
+        // four particles per thread and round, their loads issued before the first
+        // store; the rounds start at the line boundary at or below the bucket's
+        // first place, so that the waves store whole lines
         constexpr int P = 4;
-        for (int k0 = 0; k0 < count; k0 += P * kBlock) {
+        const int ahead = dsb & (MIX ? 31 : 15);
+        for (int k0 = -ahead; k0 < count; k0 += P * kBlock) {
             Raw<MIX> r[P];
 #pragma unroll
             for (int j = 0; j < P; ++j) {
-                const int k = min(k0 + j * kBlock + (int)threadIdx.x, count - 1);
+                const int k = min(max(k0 + j * kBlock + (int)threadIdx.x, 0), count - 1);
                 load_slot<MIX, DIM, VDIM>(page_at<MIX, DIM, VDIM>(t, t.tab[psb + k / kPage]), k % kPage, r[j]);
             }
 #pragma unroll
             for (int j = 0; j < P; ++j) {
                 const int k = k0 + j * kBlock + (int)threadIdx.x;
-                if (k < count) store_raw<MIX, DIM, VDIM>(dst, dsb + k, r[j]);
+                if (k >= 0 && k < count) store_raw<MIX, DIM, VDIM>(dst, dsb + k, r[j]);
             }
         }
     }
