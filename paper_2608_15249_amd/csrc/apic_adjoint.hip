@@ -47,6 +47,7 @@
 #include <cmath>
 #include <type_traits>
 #include <utility>
+#include <vector>
 
 using namespace apic;
 using namespace apic_host;
@@ -207,8 +208,11 @@ __device__ __forceinline__ void tile_coords2(const Geo &g, int b, int &bx, int &
     by = DIM == 2 ? b / g.nbx : 0;
 }
 
+// Threads of a workgroup at most: a bucket's in 1D and 2D, a plain block in 3D.
+template <int DIM> constexpr int level_block() { return DIM == 3 ? kBlock : 1024; }
+
 template <bool MIX, int DIM, int VDIM, bool HC>
-__global__ void __launch_bounds__(kBlock) k_adj_level(AdjP<typename RealOf<MIX>::T> P) {
+__global__ void __launch_bounds__(level_block<DIM>()) k_adj_level(AdjP<typename RealOf<MIX>::T> P) {
     using R = typename RealOf<MIX>::T;
     const Geo &g = P.g;
     const int64_t n = P.n;
@@ -639,14 +643,18 @@ __global__ void k_import(Geo g, int64_t n, double dx, double dy, double dz, cons
     }
 }
 
-// out[i] = src[perm[i]] (input index carried through one forward step)
-__global__ void k_adj_compose_ids(int64_t n, const int32_t *src, const int32_t *perm, int32_t *out, int *err) {
+// out[i] = src[perm_0[perm_1[... perm_{m-1}[i]]]]: input indices carried through
+// m forward steps (perm_k at perm + k * stride)
+__global__ void k_adj_chain_ids(int64_t n, const int32_t *src, const int32_t *perm, int64_t stride, int m, int32_t *out,
+                                int *err) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = perm[i];
-        if ((uint32_t)p >= (uint32_t)n) {
-            raise_err(err, ERR_ORDER);
-            out[i] = 0;
-            continue;
+        int32_t p = (int32_t)i;
+        for (int k = m - 1; k >= 0; --k) {
+            p = perm[k * stride + p];
+            if ((uint32_t)p >= (uint32_t)n) {
+                raise_err(err, ERR_ORDER);
+                p = 0;
+            }
         }
         out[i] = src[p];
     }
@@ -687,16 +695,14 @@ __global__ void k_adj_scale(int64_t m, const double *src, double *dst, double sc
         dst[i] = scale * src[i];
 }
 
-__global__ void k_adj_fill(int64_t m, double *dst) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = 0.0;
-}
-
 // lam_rho_hat = norm * (i kappa_x lam_Ex_hat + i kappa_y lam_Ey_hat
 // [+ i kappa_z lam_Ez_hat]) / K^2, 0 at k = 0; lzh NULL below 3D. lrh may be
 // lxh (each entry is read before it is written).
+// Clears lE (m words; its transforms are taken) for the next level's sums.
 __global__ void k_adj_spectral(Geo g, const double2 *lxh, const double2 *lyh, const double2 *lzh, double2 *lrh,
-                               CtxDev c) {
+                               double *lE, int64_t m, CtxDev c) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
+        lE[i] = 0.0;
     const int hx = g.nx / 2 + 1;
     const int64_t tot = (int64_t)hx * g.ny * g.nz;
     const double norm = 1.0 / ((double)g.nx * (double)g.ny * (double)g.nz);
@@ -715,12 +721,16 @@ __global__ void k_adj_spectral(Geo g, const double2 *lxh, const double2 *lyh, co
 }
 
 // 1D: lam_rho = -A lam_E with A the same Gauss-law solve as the forward field
-__global__ void __launch_bounds__(kBlock) k_adj_field1d(int nx, const double *lE, double dx, double *lrho) {
+// (lE is cleared for the next level's sums)
+__global__ void __launch_bounds__(kBlock) k_adj_field1d(int nx, double *lE, double dx, double *lrho) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sr = (double *)smem;
     __shared__ double sRed[kWaves];
     __shared__ double sScan[kBlock];
-    for (int i = threadIdx.x; i < nx; i += blockDim.x) sr[i] = lE[i];
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) {
+        sr[i] = lE[i];
+        lE[i] = 0.0;
+    }
     __syncthreads();
     (void)field1d_block(sr, nx, dx, lrho, nullptr, sRed, sScan);
     for (int i = threadIdx.x; i < nx; i += blockDim.x) lrho[i] = -lrho[i];
@@ -789,8 +799,9 @@ CkLayout ck_layout(const apic_ctx *c) {
 
 struct AdjWs {
     size_t ctx;                 // the context workspace (sort, step, field solve)
-    size_t pw_pos[4], pw_vel[3], bstart, E, E32, rho;
-    size_t id_a, id_b, inv, cross;
+    size_t pw_vel[3], pw_vel2[3];   // velocities of the levels in turn
+    size_t E32, rho;
+    size_t id_a, inv, cross;
     size_t snap_pos;            // stride entries of positions
     size_t snap_pos_bytes;
     size_t snap_perm, snap_E;   // stride entries
@@ -816,21 +827,13 @@ AdjWs adj_layout(const apic_ctx *c, int stride) {
     size_t off = 0;
     auto take = [&](size_t b) { size_t o = off; off = align256(off + b); return o; };
     L.ctx = take(c->ws_step_bytes);
-    for (auto &v : L.pw_pos) v = (size_t)-1;
     for (auto &v : L.pw_vel) v = (size_t)-1;
-    if (c->mixed) {
-        L.pw_pos[0] = take(4 * n);
-        for (int k = 0; k < dim; ++k) L.pw_pos[1 + k] = take(4 * n);
-    } else {
-        for (int k = 0; k < dim; ++k) L.pw_pos[k] = take(8 * n);
-    }
     for (int k = 0; k < vdim; ++k) L.pw_vel[k] = take(r * n);
-    L.bstart = take(4 * (c->g.nbuckets + 1));
-    L.E = take(8 * (size_t)dim * G);
+    for (auto &v : L.pw_vel2) v = (size_t)-1;
+    for (int k = 0; k < vdim; ++k) L.pw_vel2[k] = take(r * n);
     L.E32 = take(4 * (size_t)dim * G);
     L.rho = take(8 * (size_t)G);
     L.id_a = take(4 * n);
-    L.id_b = take(4 * n);
     L.inv = take(4 * n);
     L.cross = take(4 * n);
     L.snap_pos_bytes = pos_bytes(c);
@@ -885,78 +888,51 @@ PosP pos_ck(const apic_ctx *c, const CkLayout &L, char *ck) {
     return p;
 }
 
-apic_particles work_parts(const apic_ctx *c, const AdjWs &L, char *ws) {
-    apic_particles p{};
-    p.n = c->n;
+// Particle arrays of a checkpoint.
+Parts parts_ck(const apic_ctx *c, const CkLayout &L, char *ck) {
+    Parts p{};
     if (c->mixed) {
-        p.cell = wsp<int32_t>(ws, L.pw_pos[0]);
-        p.ox = wsp<float>(ws, L.pw_pos[1]);
-        p.oy = wsp<float>(ws, L.pw_pos[2]);
-        p.oz = wsp<float>(ws, L.pw_pos[3]);
+        p.cell = wsp<int32_t>(ck, L.pos[0]);
+        p.ox = wsp<float>(ck, L.pos[1]);
+        p.oy = wsp<float>(ck, L.pos[2]);
+        p.oz = wsp<float>(ck, L.pos[3]);
     } else {
-        p.x = wsp<double>(ws, L.pw_pos[0]);
-        p.y = wsp<double>(ws, L.pw_pos[1]);
-        p.z = wsp<double>(ws, L.pw_pos[2]);
+        p.x = wsp<double>(ck, L.pos[0]);
+        p.y = wsp<double>(ck, L.pos[1]);
+        p.z = wsp<double>(ck, L.pos[2]);
     }
-    p.vx = wsp<void>(ws, L.pw_vel[0]);
-    p.vy = wsp<void>(ws, L.pw_vel[1]);
-    p.vz = wsp<void>(ws, L.pw_vel[2]);
-    p.bucket_start = wsp<int32_t>(ws, L.bstart);
-    p.perm = nullptr;
+    p.vx = wsp<void>(ck, L.vel[0]);
+    p.vy = wsp<void>(ck, L.vel[1]);
+    p.vz = wsp<void>(ck, L.vel[2]);
     return p;
 }
 
-// Copy the positions of p into a position block (pos_bytes layout).
-apic_status save_pos(apic_ctx *c, const apic_particles &p, char *dst, hipStream_t s) {
-    const int64_t n = c->n;
-    if (c->mixed) {
-        const size_t a = align256(4 * n);
-        HIPCHK(c, launch_copy_bytes(dst, p.cell, 4 * n, s));
-        HIPCHK(c, launch_copy_bytes(dst + a, p.ox, 4 * n, s));
-        if (c->d.dim >= 2) HIPCHK(c, launch_copy_bytes(dst + 2 * a, p.oy, 4 * n, s));
-        if (c->d.dim == 3) HIPCHK(c, launch_copy_bytes(dst + 3 * a, p.oz, 4 * n, s));
-    } else {
-        const size_t a = align256(8 * n);
-        HIPCHK(c, launch_copy_bytes(dst, p.x, 8 * n, s));
-        if (c->d.dim >= 2) HIPCHK(c, launch_copy_bytes(dst + a, p.y, 8 * n, s));
-        if (c->d.dim == 3) HIPCHK(c, launch_copy_bytes(dst + 2 * a, p.z, 8 * n, s));
-    }
-    return APIC_OK;
-}
-
-// state <-> checkpoint (dir = +1: save, -1: load)
-apic_status ck_transfer(apic_ctx *c, const CkLayout &L, char *ck, apic_particles &p, double *E, int32_t *id,
-                        int dir, hipStream_t s) {
+// Particle arrays of level k of a segment: positions in a snapshot, velocities
+// in its [3][n] block where every level's are kept, else in one of two buffers.
+Parts parts_snap(const apic_ctx *c, const AdjWs &L, char *pos, char *vel, char *ws, int k) {
+    const PosP q = pos_block(c, pos);
     const int64_t n = c->n;
     const size_t r = c->mixed ? 4 : 8;
-    const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
-    auto mv = [&](void *state, size_t off, size_t bytes) -> hipError_t {
-        if (!state || off == (size_t)-1) return hipSuccess;
-        return dir > 0 ? launch_copy_bytes(ck + off, state, (int64_t)bytes, s)
-                       : launch_copy_bytes(state, ck + off, (int64_t)bytes, s);
-    };
-    if (c->mixed) {
-        HIPCHK(c, mv(p.cell, L.pos[0], 4 * n));
-        HIPCHK(c, mv(p.ox, L.pos[1], 4 * n));
-        HIPCHK(c, mv(p.oy, L.pos[2], 4 * n));
-        HIPCHK(c, mv(p.oz, L.pos[3], 4 * n));
-    } else {
-        HIPCHK(c, mv(p.x, L.pos[0], 8 * n));
-        HIPCHK(c, mv(p.y, L.pos[1], 8 * n));
-        HIPCHK(c, mv(p.z, L.pos[2], 8 * n));
-    }
-    HIPCHK(c, mv(p.vx, L.vel[0], r * n));
-    HIPCHK(c, mv(p.vy, L.vel[1], r * n));
-    HIPCHK(c, mv(p.vz, L.vel[2], r * n));
-    HIPCHK(c, mv(p.bucket_start, L.bstart, 4 * (size_t)(c->g.nbuckets + 1)));
-    HIPCHK(c, mv(E, L.E, 8 * (size_t)c->d.dim * G));
-    HIPCHK(c, mv(id, L.id, 4 * n));
-    return APIC_OK;
+    Parts p{};
+    p.x = const_cast<double *>(q.x);
+    p.y = const_cast<double *>(q.y);
+    p.z = const_cast<double *>(q.z);
+    p.cell = const_cast<int32_t *>(q.cell);
+    p.ox = const_cast<float *>(q.ox);
+    p.oy = const_cast<float *>(q.oy);
+    p.oz = const_cast<float *>(q.oz);
+    void *v[3] = {nullptr, nullptr, nullptr};
+    for (int d = 0; d < c->d.vdim; ++d)
+        v[d] = vel ? (void *)(vel + d * r * n) : wsp<void>(ws, k & 1 ? L.pw_vel2[d] : L.pw_vel[d]);
+    p.vx = v[0];
+    p.vy = v[1];
+    p.vz = v[2];
+    return p;
 }
 
 int n_checkpoints(int nsteps, int stride) { return (nsteps + stride - 1) / stride; }
 
-// lam_rho = A^T lam_E (FP64)
+// lam_rho = A^T lam_E (FP64); lam_E is zero afterwards
 apic_status adj_solve(apic_ctx *c, double *lE, double *lrho, char *ws_ctx, hipStream_t s) {
     const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
     if (c->d.dim == 1) {
@@ -977,7 +953,7 @@ apic_status adj_solve(apic_ctx *c, double *lE, double *lrho, char *ws_ctx, hipSt
         FFTCHK(c, hipfftExecD2Z(c->fwd, (hipfftDoubleReal *)(lE + 2 * G), (hipfftDoubleComplex *)(ehat + 16 * H)));
     hipLaunchKernelGGL(k_adj_spectral, dim3(nblocks((int64_t)H, 1024)), dim3(kBlock), 0, s, c->g,
                        (const double2 *)rhat, (const double2 *)ehat,
-                       c->d.dim == 3 ? (const double2 *)(ehat + 16 * H) : nullptr, (double2 *)rhat, c->dev);
+                       c->d.dim == 3 ? (const double2 *)(ehat + 16 * H) : nullptr, (double2 *)rhat, lE, c->d.dim * G, c->dev);
     HIPCHK(c, hipGetLastError());
     FFTCHK(c, hipfftSetStream(c->inv, s));
     FFTCHK(c, hipfftExecZ2D(c->inv, (hipfftDoubleComplex *)rhat, (hipfftDoubleReal *)lrho));
@@ -985,7 +961,7 @@ apic_status adj_solve(apic_ctx *c, double *lE, double *lrho, char *ws_ctx, hipSt
 }
 
 // Velocities of p into a [3][n] block (Higuera-Cary snapshots).
-apic_status save_vel(apic_ctx *c, const apic_particles &p, char *dst, hipStream_t s) {
+apic_status save_vel(apic_ctx *c, const Parts &p, char *dst, hipStream_t s) {
     const int64_t n = c->n;
     const size_t r = c->mixed ? 4 : 8;
     HIPCHK(c, launch_copy_bytes(dst, p.vx, (int64_t)(r * n), s));
@@ -1022,42 +998,47 @@ apic_status launch_level(apic_ctx *c, AdjP<R> &P, hipStream_t s) {
     // with the level's bucket table: one workgroup per bucket and the lam_Ep
     // scatter into an LDS tile (tile + 2-cell halo per scattered component)
     dim3 grid(nblocks(c->n));
+    int block = kBlock;
     size_t sh = 0;
     if (c->d.dim == 3) P.bs = nullptr;   // 3D scatters lam_Ep with global atomics
     if (P.bs) {
         const int tw = (1 << c->g.tsx) + 5, th = c->d.dim == 2 ? (1 << c->g.tsy) + 5 : 1;
         sh = (size_t)c->d.dim * tw * th * sizeof(double);
         grid = dim3(grid_for_buckets(c->g.nbuckets));
+        // waves for the chip where the buckets are few: up to 16 per bucket,
+        // about 32 per CU in all
+        while (block < 1024 && (int64_t)c->g.nbuckets * (2 * block / 64) <= 8192) block *= 2;
         if (sh > 65536) {
             P.bs = nullptr;
             sh = 0;
             grid = dim3(nblocks(c->n));
+            block = kBlock;
         }
     }
     if (c->d.dim == 3) {
         if (c->mixed) {
             if constexpr (std::is_same<R, float>::value) {
-                if (c->g.hc) hipLaunchKernelGGL((k_adj_level<true, 3, 3, true>), grid, dim3(kBlock), 0, s, P);
-                else hipLaunchKernelGGL((k_adj_level<true, 3, 3, false>), grid, dim3(kBlock), 0, s, P);
+                if (c->g.hc) hipLaunchKernelGGL((k_adj_level<true, 3, 3, true>), grid, dim3(block), 0, s, P);
+                else hipLaunchKernelGGL((k_adj_level<true, 3, 3, false>), grid, dim3(block), 0, s, P);
             }
         } else {
             if constexpr (std::is_same<R, double>::value) {
-                if (c->g.hc) hipLaunchKernelGGL((k_adj_level<false, 3, 3, true>), grid, dim3(kBlock), 0, s, P);
-                else hipLaunchKernelGGL((k_adj_level<false, 3, 3, false>), grid, dim3(kBlock), 0, s, P);
+                if (c->g.hc) hipLaunchKernelGGL((k_adj_level<false, 3, 3, true>), grid, dim3(block), 0, s, P);
+                else hipLaunchKernelGGL((k_adj_level<false, 3, 3, false>), grid, dim3(block), 0, s, P);
             }
         }
     } else if (c->g.hc) {
         if (c->mixed) {
             if constexpr (std::is_same<R, float>::value)
-                hipLaunchKernelGGL((k_adj_level<true, 2, 3, true>), grid, dim3(kBlock), sh, s, P);
+                hipLaunchKernelGGL((k_adj_level<true, 2, 3, true>), grid, dim3(block), sh, s, P);
         } else {
             if constexpr (std::is_same<R, double>::value)
-                hipLaunchKernelGGL((k_adj_level<false, 2, 3, true>), grid, dim3(kBlock), sh, s, P);
+                hipLaunchKernelGGL((k_adj_level<false, 2, 3, true>), grid, dim3(block), sh, s, P);
         }
     } else {
         APIC_DISPATCH_2D(c->g, c->mixed, {
             if constexpr (std::is_same<R, typename RealOf<MIX>::T>::value)
-                hipLaunchKernelGGL((k_adj_level<MIX, DIM, VDIM, false>), grid, dim3(kBlock), sh, s, P);
+                hipLaunchKernelGGL((k_adj_level<MIX, DIM, VDIM, false>), grid, dim3(block), sh, s, P);
         });
     }
     HIPCHK(c, hipGetLastError());
@@ -1085,8 +1066,7 @@ apic_status step_adjoint_impl(apic_ctx *c, char *ck, int nsteps, int stride, dou
     char *ws_ctx = ws + L.ctx;
     double *lE = wsp<double>(ws, L.lE);
     double *lrho = wsp<double>(ws, L.lrho);
-    double *E_w = wsp<double>(ws, L.E);
-    int32_t *id_w = wsp<int32_t>(ws, L.id_a), *id_t = wsp<int32_t>(ws, L.id_b);
+    int32_t *id_w = wsp<int32_t>(ws, L.id_a);
     int32_t *inv = wsp<int32_t>(ws, L.inv), *cross = wsp<int32_t>(ws, L.cross);
     const int C = n_checkpoints(nsteps, stride);
     auto ckp = [&](int k) { return ck + (size_t)k * CL.bytes; };
@@ -1105,30 +1085,32 @@ apic_status step_adjoint_impl(apic_ctx *c, char *ck, int nsteps, int stride, dou
     if (st != APIC_OK) return st;
     int cur = 0;
     bool terminal = true;
-    apic_particles pw = work_parts(c, L, ws);
+    std::vector<Level> lv;
+    std::vector<int32_t *> perms;
     for (int seg = C - 1; seg >= 0; --seg) {
         const int s0 = seg * stride, e = std::min(s0 + stride, nsteps), m = e - s0;
-        // recompute the segment from its checkpoint
-        st = ck_transfer(c, CL, ckp(seg), pw, E_w, id_w, -1, s);
-        if (st != APIC_OK) return st;
-        for (int k = 0; k < m; ++k) {
-            st = save_pos(c, pw, snap_pos(k), s);
-            if (st != APIC_OK) return st;
-            if (c->g.hc) {
-                st = save_vel(c, pw, snap_vel(k), s);
-                if (st != APIC_OK) return st;
-            }
-            HIPCHK(c, launch_copy_bytes(snap_bs(k), pw.bucket_start, (int64_t)bs_bytes, s));
-            HIPCHK(c, launch_copy_bytes(snap_E(k), E_w, 8 * (int64_t)dim * G, s));
-            pw.perm = snap_perm(k);
-            st = apic_step(c, &pw, nullptr, E_w, nullptr, 1, nullptr, ws_ctx, s);
-            pw.perm = nullptr;
-            if (st != APIC_OK) return st;
-            hipLaunchKernelGGL(k_adj_compose_ids, dim3(nblocks(n)), dim3(kBlock), 0, s, n, id_w, snap_perm(k), id_t,
-                               c->dev.err);
-            HIPCHK(c, hipGetLastError());
-            std::swap(id_w, id_t);
+        // recompute the segment from its checkpoint, every level in its snapshot
+        // (the last one, which the next checkpoint holds, in the unused slot 0)
+        lv.assign(m + 1, Level{});
+        perms.assign(m, nullptr);
+        lv[0] = Level{parts_ck(c, CL, ckp(seg)), wsp<int32_t>(ckp(seg), CL.bstart), wsp<double>(ckp(seg), CL.E)};
+        for (int k = 1; k <= m; ++k) {
+            const int slot = k < m ? k : 0;
+            lv[k] = Level{parts_snap(c, L, snap_pos(slot), c->g.hc ? snap_vel(slot) : nullptr, ws, k), snap_bs(slot),
+                          snap_E(slot)};
+            perms[k - 1] = snap_perm(k - 1);
         }
+        st = run_levels(c, lv.data(), m, perms.data(), ws_ctx, s);
+        if (st != APIC_OK) return st;
+        if (c->g.hc) {
+            // (slot 0 again: the last level's velocities are not needed)
+            st = save_vel(c, lv[0].parts, snap_vel(0), s);
+            if (st != APIC_OK) return st;
+        }
+        hipLaunchKernelGGL(k_adj_chain_ids, dim3(nblocks(n)), dim3(kBlock), 0, s, n,
+                           (const int32_t *)(ckp(seg) + CL.id), snap_perm(0), (int64_t)(align256(4 * n) / 4), m, id_w,
+                           c->dev.err);
+        HIPCHK(c, hipGetLastError());
         // the step that ends at the stored checkpoint maps through input indices
         hipLaunchKernelGGL(k_adj_invert, dim3(nblocks(n)), dim3(kBlock), 0, s, n, id_w, inv, c->dev.err);
         HIPCHK(c, hipGetLastError());
@@ -1148,7 +1130,7 @@ apic_status step_adjoint_impl(apic_ctx *c, char *ck, int nsteps, int stride, dou
             P.terminal = terminal ? 1 : 0;
             P.back = 1;
             P.perm = (lvl == e) ? cross : snap_perm(k - 1);
-            P.prev = pos_block(c, snap_pos(k - 1));
+            P.prev = k > 1 ? pos_block(c, snap_pos(k - 1)) : pos_ck(c, CL, ckp(seg));
             P.lE_prev = lE;
             P.lxp_out = wsp<R>(ws, L.lam[cur ^ 1][0]);
             P.lep_out = wsp<R>(ws, L.lam[cur ^ 1][1]);
@@ -1156,10 +1138,8 @@ apic_status step_adjoint_impl(apic_ctx *c, char *ck, int nsteps, int stride, dou
             P.init = (lvl - 1 == 0) ? 1 : 0;
             if (c->g.hc) {
                 P.vprev = (const R *)snap_vel(k - 1);
-                P.Eprev = snap_E(k - 1);
+                P.Eprev = k > 1 ? snap_E(k - 1) : (const double *)(ckp(seg) + CL.E);
             }
-            hipLaunchKernelGGL(k_adj_fill, dim3(nblocks(dim * G)), dim3(kBlock), 0, s, (int64_t)dim * G, lE);
-            HIPCHK(c, hipGetLastError());
             st = launch_level<R>(c, P, s);
             if (st != APIC_OK) return st;
             cur ^= 1;
@@ -1237,46 +1217,68 @@ apic_status apic_adjoint_forward(apic_ctx *c, const apic_particles *p0, int nste
     const int64_t n = c->n;
     const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
     const int dim = c->d.dim;
-    double *E_w = wsp<double>(w, L.E);
     float *E32_w = wsp<float>(w, L.E32);
-    int32_t *id_w = wsp<int32_t>(w, L.id_a), *id_t = wsp<int32_t>(w, L.id_b);
-    int32_t *perm = wsp<int32_t>(w, L.inv);
-    apic_particles pw = work_parts(c, L, w);
-    // x^0, v^0 in the caller's order -> sorted copy; id = input index
-    st = copy_parts(c, parts_of(&pw), parts_of(p0), s);
+    // x^0, v^0 in the caller's order -> sorted copy in the first checkpoint; id = input index
+    const Parts first = parts_ck(c, CL, ck);
+    double *E0 = wsp<double>(ck, CL.E);
+    apic_particles pw{};
+    pw.n = n;
+    pw.x = first.x;
+    pw.y = first.y;
+    pw.z = first.z;
+    pw.cell = first.cell;
+    pw.ox = first.ox;
+    pw.oy = first.oy;
+    pw.oz = first.oz;
+    pw.vx = first.vx;
+    pw.vy = first.vy;
+    pw.vz = first.vz;
+    pw.bucket_start = wsp<int32_t>(ck, CL.bstart);
+    st = copy_parts(c, first, parts_of(p0), s);
     if (st != APIC_OK) return st;
-    pw.perm = id_w;
+    pw.perm = wsp<int32_t>(ck, CL.id);
     st = apic_sort_by_cell(c, &pw, ws_ctx, s);
     pw.perm = nullptr;
     if (st != APIC_OK) return st;
     // E^0, then the backward half push
     st = apic_deposit(c, &pw, wsp<void>(w, L.rho), s);
     if (st != APIC_OK) return st;
-    st = apic_field_solve(c, wsp<void>(w, L.rho), E_w, c->mixed ? E32_w : nullptr, nullptr, ws_ctx, s);
+    st = apic_field_solve(c, wsp<void>(w, L.rho), E0, c->mixed ? E32_w : nullptr, nullptr, ws_ctx, s);
     if (st != APIC_OK) return st;
-    st = apic_gather_push(c, &pw, c->mixed ? (const void *)E32_w : (const void *)E_w, -0.5, 0, s);
+    st = apic_gather_push(c, &pw, c->mixed ? (const void *)E32_w : (const void *)E0, -0.5, 0, s);
     if (st != APIC_OK) return st;
-    st = ck_transfer(c, CL, ck, pw, E_w, id_w, +1, s);
-    if (st != APIC_OK) return st;
-    for (int k = 0; k < nsteps; ++k) {
-        pw.perm = perm;
-        st = apic_step(c, &pw, nullptr, E_w, nullptr, 1, nullptr, ws_ctx, s);
-        pw.perm = nullptr;
-        if (st != APIC_OK) return st;
-        hipLaunchKernelGGL(k_adj_compose_ids, dim3(nblocks(n)), dim3(kBlock), 0, s, n, id_w, perm, id_t, c->dev.err);
-        HIPCHK(c, hipGetLastError());
-        std::swap(id_w, id_t);
-        if ((k + 1) % stride == 0 || k + 1 == nsteps) {
-            const int idx = (k + 1 + stride - 1) / stride;
-            st = ck_transfer(c, CL, ck + (size_t)idx * CL.bytes, pw, E_w, id_w, +1, s);
-            if (st != APIC_OK) return st;
+    // segment by segment between the checkpoints: the last level of each is
+    // written straight into its checkpoint
+    std::vector<Level> lv;
+    std::vector<int32_t *> perms;
+    const size_t perm_bytes = align256(4 * n);
+    const double *E_last = E0;
+    for (int s0 = 0, idx = 1; s0 < nsteps; s0 += stride, ++idx) {
+        const int m = std::min(stride, nsteps - s0);
+        char *from = ck + (size_t)(idx - 1) * CL.bytes, *to = ck + (size_t)idx * CL.bytes;
+        lv.assign(m + 1, Level{});
+        perms.assign(m, nullptr);
+        lv[0] = Level{parts_ck(c, CL, from), wsp<int32_t>(from, CL.bstart), wsp<double>(from, CL.E)};
+        for (int k = 1; k < m; ++k) {
+            const int slot = k % 2 < stride ? k % 2 : 0;   // levels in between are not kept: two slots in turn
+            lv[k] = Level{parts_snap(c, L, w + L.snap_pos + slot * L.snap_pos_bytes, nullptr, w, k),
+                          (int32_t *)(w + L.snap_bs + slot * align256(4 * (size_t)(c->g.nbuckets + 1))),
+                          (double *)(w + L.snap_E + slot * align256(8 * (size_t)dim * G))};
         }
+        lv[m] = Level{parts_ck(c, CL, to), wsp<int32_t>(to, CL.bstart), wsp<double>(to, CL.E)};
+        for (int k = 0; k < m; ++k) perms[k] = (int32_t *)(w + L.snap_perm + k * perm_bytes);
+        st = run_levels(c, lv.data(), m, perms.data(), ws_ctx, s);
+        if (st != APIC_OK) return st;
+        hipLaunchKernelGGL(k_adj_chain_ids, dim3(nblocks(n)), dim3(kBlock), 0, s, n, wsp<int32_t>(from, CL.id), perms[0],
+                           (int64_t)(perm_bytes / 4), m, wsp<int32_t>(to, CL.id), c->dev.err);
+        HIPCHK(c, hipGetLastError());
+        E_last = lv[m].E;
     }
     if (W) {
-        hipLaunchKernelGGL(k_adj_energy, dim3(1), dim3(1024), 0, s, (int64_t)dim * G, E_w, c->dV, W);
+        hipLaunchKernelGGL(k_adj_energy, dim3(1), dim3(1024), 0, s, (int64_t)dim * G, E_last, c->dV, W);
         HIPCHK(c, hipGetLastError());
     }
-    if (E_out) HIPCHK(c, launch_copy_bytes(E_out, E_w, 8 * (int64_t)dim * G, s));
+    if (E_out) HIPCHK(c, launch_copy_bytes(E_out, E_last, 8 * (int64_t)dim * G, s));
     return APIC_OK;
 }
 

@@ -765,6 +765,16 @@ apic_status apic_gather_push(apic_ctx *c, apic_particles *p, const void *E, doub
 
 namespace apic_host {
 
+// The caller's rho (NULL: none) from the charge of a step.
+apic_status rho_out(apic_ctx *c, void *rho, void *acc, hipStream_t s) {
+    if (!rho) return APIC_OK;
+    if (c->mixed)
+        HIPCHK(c, launch_copy_bytes(rho, acc, 8 * (int64_t)c->d.nx * c->d.ny * c->d.nz, s));
+    else
+        HIPCHK(c, launch_rho(c->g, false, acc, (double *)rho, acc_scale(c), c->d.rho_ion, 0, nullptr, s));
+    return APIC_OK;
+}
+
 // nsteps cycles on paged particles (apic_pages.hip): from p to dst and its
 // bucket table bs_dst (p itself, or the second buffer).
 apic_status step_paged(apic_ctx *c, apic_particles *p, const Parts &dst, int32_t *bs_dst, void *rho, double *E,
@@ -785,12 +795,8 @@ apic_status step_paged(apic_ctx *c, apic_particles *p, const Parts &dst, int32_t
         HIPCHK(c, launch_page_push(c->g, c->mixed, t, k == 0 ? &A : nullptr, p->bucket_start, c->n, max_per_bucket(c),
                                    E, k > 0 ? e32 : nullptr, pc, acc, diag ? c->dev.part_push : nullptr, c->dev, s));
         if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
-        if (rho && last) {
-            if (c->mixed)
-                HIPCHK(c, launch_copy_bytes(rho, acc, 8 * G, s));
-            else
-                HIPCHK(c, launch_rho(c->g, false, acc, (double *)rho, acc_scale(c), c->d.rho_ion, 0, nullptr, s));
-        }
+        st = rho_out(c, last ? rho : nullptr, acc, s);
+        if (st != APIC_OK) return st;
         st = field_from_acc(c, acc, false, (last || !e32) ? E : nullptr, last ? E32 : e32, diag, nullptr, nullptr,
                             diag ? nb : 0, 1, ws, s, t.live);
         if (st != APIC_OK) return st;
@@ -800,68 +806,89 @@ apic_status step_paged(apic_ctx *c, apic_particles *p, const Parts &dst, int32_t
     return APIC_OK;
 }
 
+// What a reordering step adds to, cleared for a run of steps: far counters, the
+// two alternating bucket totals, deep ranges (none known for the incoming order:
+// the first count reads all) and the charge.
+apic_status begin_reordering(apic_ctx *c, void *ws, hipStream_t s) {
+    const int nb = c->g.nbuckets;
+    const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
+    HIPCHK(c, launch_fill_i32(wsp<int32_t>(ws, c->o_farcnt), nb, 0, s));
+    HIPCHK(c, launch_fill_i32(wsp<int32_t>(ws, c->o_tot), 2 * (int64_t)nb, 0, s));
+    HIPCHK(c, launch_fill_i32(wsp<int32_t>(ws, c->o_deep), (int64_t)nb * kDeepTab, 0, s));
+    HIPCHK(c, launch_fill_u64(wsp<uint64_t>(ws, c->o_acc), G, 0, s));
+    HIPCHK(c, launch_set_step(c->dev.step, -1, s));
+    return APIC_OK;
+}
+
+// Count, scan and push of step k of a run: src in the order of bs_src to dst in
+// the order of bs_dst (written).
+apic_status reorder_step(apic_ctx *c, int k, const Parts &src, const Parts &dst, int32_t *bs_src, int32_t *bs_dst,
+                         const double *E, const float *E32, const PushC &pc, int32_t *perm, bool diag, hipEvent_t *ev,
+                         void *ws, hipStream_t s) {
+    const int nb = c->g.nbuckets;
+    int32_t *cnt = wsp<int32_t>(ws, c->o_cnt), *offs = wsp<int32_t>(ws, c->o_offs);
+    int32_t *farcnt = wsp<int32_t>(ws, c->o_farcnt), *deep = wsp<int32_t>(ws, c->o_deep);
+    int32_t *tot = wsp<int32_t>(ws, c->o_tot);
+    int32_t *tot_k = tot + (k & 1 ? nb : 0), *tot_n = tot + (k & 1 ? 0 : nb);
+    if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[0], s));
+    HIPCHK(c, launch_step_count(c->g, c->mixed, src, bs_src, E, E32, pc, cnt, tot_k, farcnt, deep, c->dev, s));
+    if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[1], s));
+    if (fused_scan_offsets(c->g)) {
+        HIPCHK(c, launch_scan_offsets(c->g, tot_k, tot_n, bs_dst, c->n, max_per_bucket(c), 1, cnt, offs, c->dev, s));
+    } else {
+        HIPCHK(c, launch_scan_dir(c->g, tot_k, bs_dst, c->n, max_per_bucket(c), 1, c->dev, s));
+        HIPCHK(c, launch_dest_offsets(c->g, cnt, bs_dst, offs, s));
+    }
+    if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
+    HIPCHK(c, launch_step_push(c->g, c->mixed, src, dst, bs_src, bs_dst, cnt, offs, farcnt, E, E32, pc,
+                               wsp<void>(ws, c->o_acc), perm, diag ? c->dev.part_push : nullptr, deep, c->dev, s));
+    if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
+    return APIC_OK;
+}
+
+apic_status run_levels(apic_ctx *c, const Level *lv, int m, int32_t *const *perm, void *ws, hipStream_t s) {
+    const PushC pc = push_coeffs(c, 1.0, 1);
+    apic_status st = begin_reordering(c, ws, s);
+    for (int k = 0; k < m && st == APIC_OK; ++k) {
+        hipEvent_t *ev = profile_events(c, false);
+        st = reorder_step(c, k, lv[k].parts, lv[k + 1].parts, lv[k].bstart, lv[k + 1].bstart, lv[k].E, nullptr, pc,
+                          perm[k], false, ev, ws, s);
+        if (st != APIC_OK) break;
+        st = field_from_acc(c, wsp<void>(ws, c->o_acc), false, lv[k + 1].E, nullptr, nullptr, nullptr, nullptr, 0, 1, ws,
+                            s, lv[k + 1].bstart + c->g.nbuckets);
+        if (st == APIC_OK && ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[4], s));
+    }
+    return st;
+}
+
 // nsteps cycles alternating between the particle buffers A (p, holding the
 // state on entry) and B with its bucket table bsB; after an odd count the
 // state is in B, and copy_back moves it to p.
 // ws_pages: ws holds the whole workspace, the paged storage included.
 apic_status step_run(apic_ctx *c, apic_particles *p, const Parts &B, int32_t *bsB, bool copy_back, void *rho,
                      double *E, float *E32, int nsteps, double *diag, void *ws, bool ws_pages, hipStream_t s) {
-    apic_status st = APIC_OK;
     const int nb = c->g.nbuckets;
-    const int64_t G = (int64_t)c->d.nx * c->d.ny * c->d.nz;
-    int32_t *cnt = wsp<int32_t>(ws, c->o_cnt);
-    int32_t *offs = wsp<int32_t>(ws, c->o_offs);
-    int32_t *farcnt = wsp<int32_t>(ws, c->o_farcnt);
-    int32_t *tot = wsp<int32_t>(ws, c->o_tot);
-    int32_t *deep = wsp<int32_t>(ws, c->o_deep);
-    void *acc = wsp<void>(ws, c->o_acc);
     if (nsteps >= kPagedSteps && c->npages && !p->perm && ws_pages) {
         const bool to_b = (nsteps & 1) && !copy_back;
         return step_paged(c, p, to_b ? B : parts_of(p), to_b ? bsB : p->bucket_start, rho, E, E32, nsteps, diag, ws, s);
     }
+    void *acc = wsp<void>(ws, c->o_acc);
     const Parts A = parts_of(p);
     int32_t *bsA = p->bucket_start;
     const PushC pc = push_coeffs(c, 1.0, 1);
     // binary32 E between the steps of the mixed path (2D and 3D)
     float *e32 = c->o_e32 != (size_t)-1 ? wsp<float>(ws, c->o_e32) : nullptr;
-    HIPCHK(c, launch_fill_i32(farcnt, nb, 0, s));
-    // the bucket totals: two buffers, alternating by step
-    HIPCHK(c, launch_fill_i32(tot, 2 * (int64_t)nb, 0, s));
-    // no deep ranges known for the incoming order: the first count reads all
-    HIPCHK(c, launch_fill_i32(deep, (int64_t)nb * kDeepTab, 0, s));
-    HIPCHK(c, launch_fill_u64((uint64_t *)acc, G, 0, s));
-    HIPCHK(c, launch_set_step(c->dev.step, -1, s));
+    apic_status st = begin_reordering(c, ws, s);
+    if (st != APIC_OK) return st;
     for (int k = 0; k < nsteps; ++k) {
-        const bool even = (k & 1) == 0;
-        const Parts &src = even ? A : B;
-        const Parts &dst = even ? B : A;
-        int32_t *bs_src = even ? bsA : bsB;
+        const bool even = (k & 1) == 0, last = k == nsteps - 1;
         int32_t *bs_dst = even ? bsB : bsA;
-        const bool last = k == nsteps - 1;
         hipEvent_t *ev = profile_events(c, false);
-        if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[0], s));
-        int32_t *tot_k = tot + (even ? 0 : nb), *tot_n = tot + (even ? nb : 0);
-        HIPCHK(c, launch_step_count(c->g, c->mixed, src, bs_src, E, k > 0 ? e32 : nullptr, pc, cnt, tot_k, farcnt,
-                                    deep, c->dev, s));
-        if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[1], s));
-        if (fused_scan_offsets(c->g)) {
-            HIPCHK(c, launch_scan_offsets(c->g, tot_k, tot_n, bs_dst, c->n, max_per_bucket(c), 1, cnt, offs, c->dev,
-                                          s));
-        } else {
-            HIPCHK(c, launch_scan_dir(c->g, tot_k, bs_dst, c->n, max_per_bucket(c), 1, c->dev, s));
-            HIPCHK(c, launch_dest_offsets(c->g, cnt, bs_dst, offs, s));
-        }
-        if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
-        HIPCHK(c, launch_step_push(c->g, c->mixed, src, dst, bs_src, bs_dst, cnt, offs, farcnt, E,
-                                   k > 0 ? e32 : nullptr, pc, acc, p->perm, diag ? c->dev.part_push : nullptr, deep,
-                                   c->dev, s));
-        if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
-        if (rho && last) {
-            if (c->mixed)
-                HIPCHK(c, launch_copy_bytes(rho, acc, 8 * G, s));
-            else
-                HIPCHK(c, launch_rho(c->g, false, acc, (double *)rho, acc_scale(c), c->d.rho_ion, 0, nullptr, s));
-        }
+        st = reorder_step(c, k, even ? A : B, even ? B : A, even ? bsA : bsB, bs_dst, E, k > 0 ? e32 : nullptr, pc,
+                          p->perm, diag != nullptr, ev, ws, s);
+        if (st != APIC_OK) return st;
+        st = rho_out(c, last ? rho : nullptr, acc, s);
+        if (st != APIC_OK) return st;
         // mixed path: between steps only the binary32 field (the push reads no
         // more); the FP64 E (and the caller's E32) after the last step
         st = field_from_acc(c, acc, false, (last || !e32) ? E : nullptr, last ? E32 : e32, diag, nullptr, nullptr,

@@ -100,6 +100,15 @@ apic::PageStep page_step(const apic_ctx *c, void *ws, int k);
 apic_status page_begin(apic_ctx *c, const int32_t *bstart, void *acc, int64_t nacc, void *ws, hipStream_t s);
 // Events of the step about to run (NULL: not profiled); paged: it keeps the particles in place.
 hipEvent_t *profile_events(apic_ctx *c, bool paged);
+// Particles, bucket table and field of one time level, in arrays of the caller's choice.
+struct Level {
+    Parts parts;
+    int32_t *bstart;
+    double *E;
+};
+// Steps from lv[0] to lv[m], each level left where lv says; perm[k]: the
+// reordering of step k (as apic_particles::perm).
+apic_status run_levels(apic_ctx *c, const Level *lv, int m, int32_t *const *perm, void *ws, hipStream_t s);
 apic_status copy_parts(apic_ctx *c, const Parts &dst, const Parts &src, hipStream_t s);
 
 }  // namespace apic_host
