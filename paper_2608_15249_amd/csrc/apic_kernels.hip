@@ -31,6 +31,7 @@
 //  * This file is compiled with -ffp-contract=off: the count pass and the push
 //    pass must produce identical bits for the same particle.
 #include <algorithm>
+#include <type_traits>
 
 #include "apic_step.h"
 
@@ -322,17 +323,18 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, co
 // particles run the full computation and are tallied with LDS atomics.
 // EM: the electromagnetic form (FP64 2D3V): E is the [6][G] Yee field.
 // E32 (mixed path, may be NULL): E already rounded to binary32, read instead.
-template <bool MIX, int DIM, int VDIM, int U, bool HC, bool EM>
-__global__ void __launch_bounds__(kSBlock) k_step_count(Geo g, Parts p, const int32_t *bstart, const double *E,
+template <bool MIX, int DIM, int VDIM, int U, bool HC, bool EM, int SW>
+__global__ void __launch_bounds__(64 * SW) k_step_count(Geo g, Parts p, const int32_t *bstart, const double *E,
                                                        const float *E32, PushC pc, int32_t *cnt, int32_t *tot, int32_t *farcnt,
                                                        const int32_t *deep, CtxDev c) {
+    constexpr int kSB = 64 * SW;
     static_assert(!EM || (DIM == 2 && VDIM == 3), "the electromagnetic step is 2D3V");
     using R = typename Pt<MIX>::R;
     constexpr int kFar = Dir<DIM>::kFar, kStay = Dir<DIM>::kStay, kTab = Dir<DIM>::kTab;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int sErr;
     __shared__ int32_t sCnt[kTab];
-    __shared__ float sMax[kSWaves][3];
+    __shared__ float sMax[SW][3];
     R *sE = (R *)smem;
     const int w = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
@@ -404,7 +406,7 @@ __global__ void __launch_bounds__(kSBlock) k_step_count(Geo g, Parts p, const in
         }
         __syncthreads();
         float emx = 0.0f, emy = 0.0f, emz = 0.0f;
-        for (int w2 = 0; w2 < kSWaves; ++w2) {
+        for (int w2 = 0; w2 < SW; ++w2) {
             emx = fmaxf(emx, sMax[w2][0]);
             emy = fmaxf(emy, sMax[w2][1]);
             emz = fmaxf(emz, sMax[w2][2]);
@@ -457,20 +459,20 @@ __global__ void __launch_bounds__(kSBlock) k_step_count(Geo g, Parts p, const in
             };
             Raw<MIX> sa, sb;
             if (nsh > 0) sfetch(sa, threadIdx.x);
-            for (int t0 = 0; t0 < nsh; t0 += 2 * kSBlock) {
-                if (t0 + kSBlock < nsh) sfetch(sb, t0 + kSBlock + threadIdx.x);
+            for (int t0 = 0; t0 < nsh; t0 += 2 * kSB) {
+                if (t0 + kSB < nsh) sfetch(sb, t0 + kSB + threadIdx.x);
                 sprocess(sa, t0 + threadIdx.x);
-                if (t0 + 2 * kSBlock < nsh) sfetch(sa, t0 + 2 * kSBlock + threadIdx.x);
-                if (t0 + kSBlock < nsh) sprocess(sb, t0 + kSBlock + threadIdx.x);
+                if (t0 + 2 * kSB < nsh) sfetch(sa, t0 + 2 * kSB + threadIdx.x);
+                if (t0 + kSB < nsh) sprocess(sb, t0 + kSB + threadIdx.x);
             }
         } else {
         // two register sets, each chunk's loads issued one chunk ahead of its use
-        constexpr int CH = kSBlock * U;
+        constexpr int CH = kSB * U;
         Raw<MIX> ra[U], rb[U];
         auto fetch = [&](Raw<MIX> *r, int base) {
 #pragma unroll
             for (int j = 0; j < U; ++j)
-                load_raw<MIX, DIM, VDIM>(p, i0 + min(max(base + j * kSBlock + (int)threadIdx.x - sh, 0), span - 1),
+                load_raw<MIX, DIM, VDIM>(p, i0 + min(max(base + j * kSB + (int)threadIdx.x - sh, 0), span - 1),
                                          r[j]);
             // keep these loads where they are: issued one chunk ahead of their use
             __builtin_amdgcn_sched_barrier(0);
@@ -478,7 +480,7 @@ __global__ void __launch_bounds__(kSBlock) k_step_count(Geo g, Parts p, const in
         auto process = [&](Raw<MIX> *r, int base) {
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const int k = base + j * kSBlock + (int)threadIdx.x - sh;
+                const int k = base + j * kSB + (int)threadIdx.x - sh;
                 const bool act = k >= 0 && k < span;
                 int code = -1, nbk = 0;
                 if (act) {
@@ -642,29 +644,30 @@ __global__ void __launch_bounds__(kSBlock) k_scan_offsets(Geo g, const int32_t *
 template <bool MIX, bool HC, bool EM>
 constexpr int push_waves() { return (MIX && EM && !HC) ? 5 : 1; }
 
-template <bool MIX, int DIM, int VDIM, int U, bool HC, bool EM, bool VR = false>
-__global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_push(Geo g, Parts src, Parts dst, const int32_t *bstart,
+template <bool MIX, int DIM, int VDIM, int U, bool HC, bool EM, int SW, bool VR = false>
+__global__ void __launch_bounds__(64 * SW, (push_waves<MIX, HC, EM>())) k_step_push(Geo g, Parts src, Parts dst, const int32_t *bstart,
                                                       const int32_t *bstart_new, const int32_t *cnt,
                                                       const int32_t *offs, int32_t *farcnt, const double *E,
                                                       const float *E32, PushC pc,
                                                       typename AccOf<MIX>::T *acc, int32_t *perm, double *part,
                                                       int32_t *deep_out, CtxDev c) {
+    constexpr int kSB = 64 * SW;
     using R = typename Pt<MIX>::R;
     using A = typename AccOf<MIX>::T;
     constexpr int kFar = Dir<DIM>::kFar, kStay = Dir<DIM>::kStay, kTab = Dir<DIM>::kTab;
     constexpr int kCodeBits = Dir<DIM>::kCodeBits;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int sErr;
-    __shared__ double sRed[kSWaves];
+    __shared__ double sRed[SW];
     __shared__ int32_t sRunEnd[kTab];  // end of each direction's slot range
     __shared__ int32_t sEnd[kFar];     // end of each destination bucket (slot bound)
     __shared__ int32_t sStay[2];       // the stay range [first, end)
-    __shared__ int32_t sCur[kSWaves][kTab];  // each wave's copy of the movers' next slots
+    __shared__ int32_t sCur[SW][kTab];  // each wave's copy of the movers' next slots
     // per-chunk counts, double-buffered by chunk parity: each wave's movers per
     // direction (valid when its flag is set) and a packed word with its deep
     // count, shallow count and mover flag
-    __shared__ int32_t sMv[2][kSWaves][kTab];
-    __shared__ int32_t sPk[2][kSWaves];
+    __shared__ int32_t sMv[2][SW][kTab];
+    __shared__ int32_t sPk[2][SW];
     const int ex_w = (1 << g.tsx) + 1, ey_w = (DIM >= 2) ? (1 << g.tsy) + 1 : 1;
     const int ez_w = (DIM == 3) ? (1 << g.tsz) + 1 : 1;
     const int wx = (1 << g.tsx) + 1 + 2 * g.halo;
@@ -689,9 +692,9 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
     const int pwx = vreg<kVc>(wx), pwy = vreg<kVc>(wy), pwxy = vreg<kVc>(wxy);
     const int pex = vreg<kVc>(ex_w), pey = vreg<kVc>(ey_w), pez = vreg<kVc>(ez_w);
     // all ones for the waves before this one (their counts come first)
-    int before[kSWaves];
+    int before[SW];
 #pragma unroll
-    for (int w2 = 0; w2 < kSWaves; ++w2) before[w2] = vreg<kVt || (MIX && EM)>(w2 < w ? -1 : 0);
+    for (int w2 = 0; w2 < SW; ++w2) before[w2] = vreg<kVt || (MIX && EM)>(w2 < w ? -1 : 0);
     if (threadIdx.x == 0) sErr = 0;
     int first, end, stride;
     bucket_walk(g.nbuckets, first, end, stride);
@@ -742,7 +745,7 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
         auto fetch = [&](Raw<MIX> *r, int base) {
 #pragma unroll
             for (int j = 0; j < U; ++j)
-                load_raw<MIX, DIM, VDIM>(src, i0 + min(max(base + j * kSBlock + (int)threadIdx.x - sh, 0), span - 1),
+                load_raw<MIX, DIM, VDIM>(src, i0 + min(max(base + j * kSB + (int)threadIdx.x - sh, 0), span - 1),
                                          r[j]);
             // keep these loads where they are: issued one chunk ahead of their use
             __builtin_amdgcn_sched_barrier(0);
@@ -767,7 +770,7 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
                 }
             }
 #pragma unroll
-            for (int w2 = 0; w2 < kSWaves; ++w2) sCur[w2][d] = off;
+            for (int w2 = 0; w2 < SW; ++w2) sCur[w2][d] = off;
             sRunEnd[d] = off + ct;
         }
         if constexpr (EM)
@@ -788,7 +791,7 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
         const float tye = (float)tn.tye;
         const float tze = (float)tn.tze;
         double ke = 0.0, px = 0.0;
-        constexpr int CH = kSBlock * U;
+        constexpr int CH = kSB * U;
         // Two schedules over chunks of CH particles.
         // FP64 (twice the bytes per particle, latency-exposed): a software
         // pipeline whose loads of chunk c+1 and stores of chunk c-1 are both
@@ -820,7 +823,7 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
         auto process = [&](const Raw<MIX> *r, int base) {
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const int k = base + j * kSBlock + (int)threadIdx.x - sh;
+                const int k = base + j * kSB + (int)threadIdx.x - sh;
                 const bool act = k >= 0 && k < span;
                 int code = -1, nbk = 0;
                 bool deep = false;
@@ -957,14 +960,14 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
                 }
                 // packed: deep count in bits 0-9, shallow count in bits 10-19, the
                 // mover flag from bit 20 (sums over the waves stay below 1024)
-                static_assert(kSBlock < 1024, "a chunk's counts fill ten bits");
+                static_assert(kSB < 1024, "a chunk's counts fill ten bits");
                 if (lane == 0) sPk[par][w] = nd | (ns << 10) | ((gmv != 0) << 20);
                 __syncthreads();
                 // the counts of the waves before this one, and of the whole chunk,
                 // summed as packed words
-                int pk[kSWaves], pre = 0, tot = 0;
+                int pk[SW], pre = 0, tot = 0;
 #pragma unroll
-                for (int w2 = 0; w2 < kSWaves; ++w2) {
+                for (int w2 = 0; w2 < SW; ++w2) {
                     pk[w2] = sPk[par][w2];
                     tot += pk[w2];
                     pre += pk[w2] & before[w2];
@@ -988,7 +991,7 @@ __global__ void __launch_bounds__(kSBlock, (push_waves<MIX, HC, EM>())) k_step_p
                     if (lane < kTab) {
                         int mpre = 0, mtot = 0;
 #pragma unroll
-                        for (int w2 = 0; w2 < kSWaves; ++w2) {
+                        for (int w2 = 0; w2 < SW; ++w2) {
                             const int c2 = (pk[w2] >> 20) ? sMv[par][w2][lane] : 0;
                             mpre += c2 & before[w2];
                             mtot += c2;
@@ -1375,26 +1378,38 @@ hipError_t launch_gather_push(const Geo &g, bool mixed, const Parts &p, int64_t 
     return hipGetLastError();
 }
 
+// Waves per bucket of the count and push passes: kSWaves, or twice as many with
+// at most two buckets per CU, which leave its SIMDs short of waves. Per step in
+// calls of 6 steps: two-stream 64 x 64, 0.52M mixed in 128 buckets 61.5 -> 51.4 us,
+// 1.0M FP64 in 437 buckets 84.2 -> 80.2 us; but 4.2M mixed between walls in 1024
+// buckets 86.4 -> 92.4 us. The order the push leaves does not depend on it: slots
+// go out in input order.
+template <typename F>
+void with_step_waves(const Geo &g, F go) {
+    if (g.nbuckets <= 2 * cu_count()) go(std::integral_constant<int, 2 * kSWaves>{});
+    else go(std::integral_constant<int, kSWaves>{});
+}
+
 hipError_t launch_step_count(const Geo &g, bool mixed, const Parts &p, const int32_t *bstart, const double *E,
                              const float *E32, const PushC &pc, int32_t *cnt, int32_t *tot, int32_t *farcnt,
                              const int32_t *deep, const CtxDev &c, hipStream_t s) {
+    auto launch = [&](auto kern, int block, size_t sh, const float *e32) {
+        hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, sh, g.nbuckets, block)), dim3(block), sh, s, g, p, bstart,
+                           E, e32, pc, cnt, tot, farcnt, deep, c);
+    };
     if (g.em) {
         const size_t sh = em_f_tile_bytes(g, mixed);
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, sh, g.nbuckets, kSBlock)), dim3(kSBlock), sh, s, g, p, bstart,
-                               E, nullptr, pc, cnt, tot, farcnt, deep, c);
-        };
-        if (mixed && g.hc) go(k_step_count<true, 2, 3, APIC_STEP_U, true, true>);
-        else if (mixed) go(k_step_count<true, 2, 3, APIC_STEP_U, false, true>);
-        else if (g.hc) go(k_step_count<false, 2, 3, APIC_STEP_U, true, true>);
-        else go(k_step_count<false, 2, 3, APIC_STEP_U, false, true>);
+        auto go = [&](auto kern) { launch(kern, kSBlock, sh, nullptr); };
+        if (mixed && g.hc) go(k_step_count<true, 2, 3, APIC_STEP_U, true, true, kSWaves>);
+        else if (mixed) go(k_step_count<true, 2, 3, APIC_STEP_U, false, true, kSWaves>);
+        else if (g.hc) go(k_step_count<false, 2, 3, APIC_STEP_U, true, true, kSWaves>);
+        else go(k_step_count<false, 2, 3, APIC_STEP_U, false, true, kSWaves>);
         return hipGetLastError();
     }
-    size_t sh = tile_e_bytes(g, mixed);
-    APIC_DISPATCH(g, mixed, {
-        auto kern = k_step_count<MIX, DIM, VDIM, U, HC, false>;
-        hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, sh, g.nbuckets, kSBlock)), dim3(kSBlock), sh, s, g, p, bstart, E,
-                           MIX ? E32 : nullptr, pc, cnt, tot, farcnt, deep, c);
+    const size_t sh = tile_e_bytes(g, mixed);
+    with_step_waves(g, [&](auto sw) {
+        constexpr int SW = decltype(sw)::value;
+        APIC_DISPATCH(g, mixed, launch(k_step_count<MIX, DIM, VDIM, U, HC, false, SW>, 64 * SW, sh, MIX ? E32 : nullptr));
     });
     return hipGetLastError();
 }
@@ -1441,39 +1456,41 @@ hipError_t launch_step_push(const Geo &g, bool mixed, const Parts &src, const Pa
                             const int32_t *bstart_new, const int32_t *cnt, const int32_t *offs, int32_t *farcnt,
                             const double *E, const float *E32, const PushC &pc, void *acc, int32_t *perm,
                             double *part, int32_t *deep, const CtxDev &c, hipStream_t s) {
+    auto launch = [&](auto kern, int block, size_t sh, const float *e32, auto *accp) {
+        hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, sh, g.nbuckets, block)), dim3(block), sh, s, g, src, dst,
+                           bstart, bstart_new, cnt, offs, farcnt, E, e32, pc, accp, perm, part, deep, c);
+    };
     if (g.em) {
         const size_t sh = em_j_tile_bytes(g) + em_f_tile_bytes(g, mixed);
-        auto go = [&](auto kern, auto *accp) {
-            hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, sh, g.nbuckets, kSBlock)), dim3(kSBlock), sh, s, g, src, dst,
-                               bstart, bstart_new, cnt, offs, farcnt, E, nullptr, pc, accp, perm, part, deep, c);
-        };
+        auto go = [&](auto kern, auto *accp) { launch(kern, kSBlock, sh, nullptr, accp); };
         unsigned long long *am = (unsigned long long *)acc;
         double *ad = (double *)acc;
-        if (mixed && g.hc) go(k_step_push<true, 2, 3, APIC_STEP_U, true, true>, am);
-        else if (mixed) go(k_step_push<true, 2, 3, APIC_STEP_U, false, true>, am);
-        else if (g.hc) go(k_step_push<false, 2, 3, APIC_STEP_U, true, true>, ad);
-        else go(k_step_push<false, 2, 3, APIC_STEP_U, false, true>, ad);
+        if (mixed && g.hc) go(k_step_push<true, 2, 3, APIC_STEP_U, true, true, kSWaves>, am);
+        else if (mixed) go(k_step_push<true, 2, 3, APIC_STEP_U, false, true, kSWaves>, am);
+        else if (g.hc) go(k_step_push<false, 2, 3, APIC_STEP_U, true, true, kSWaves>, ad);
+        else go(k_step_push<false, 2, 3, APIC_STEP_U, false, true, kSWaves>, ad);
         return hipGetLastError();
     }
-    size_t sh = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
-    APIC_DISPATCH(g, mixed, {
-        auto kern = k_step_push<MIX, DIM, VDIM, U, HC, false>;
-        auto run = [&](auto k) {
-            hipLaunchKernelGGL(k, dim3(persistent_grid(k, sh, g.nbuckets, kSBlock)), dim3(kSBlock), sh, s, g, src,
-                               dst, bstart, bstart_new, cnt, offs, farcnt, E, MIX ? E32 : nullptr, pc,
-                               (typename AccOf<MIX>::T *)acc, perm, part, deep, c);
-        };
-        if constexpr (MIX && !HC) {
-            auto kvr = k_step_push<MIX, DIM, VDIM, U, HC, false, true>;
-            if (g.push_vr == 2 ||
-                (g.push_vr == 0 &&
-                 resident_per_cu(kvr, sh, g.nbuckets, kSBlock) >= resident_per_cu(kern, sh, g.nbuckets, kSBlock)))
-                run(kvr);
-            else
+    const size_t sh = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
+    with_step_waves(g, [&](auto sw) {
+        constexpr int SW = decltype(sw)::value;
+        APIC_DISPATCH(g, mixed, {
+            auto kern = k_step_push<MIX, DIM, VDIM, U, HC, false, SW>;
+            auto run = [&](auto k) {
+                launch(k, 64 * SW, sh, MIX ? E32 : nullptr, (typename AccOf<MIX>::T *)acc);
+            };
+            if constexpr (MIX && !HC) {
+                auto kvr = k_step_push<MIX, DIM, VDIM, U, HC, false, SW, true>;
+                if (g.push_vr == 2 ||
+                    (g.push_vr == 0 &&
+                     resident_per_cu(kvr, sh, g.nbuckets, 64 * SW) >= resident_per_cu(kern, sh, g.nbuckets, 64 * SW)))
+                    run(kvr);
+                else
+                    run(kern);
+            } else {
                 run(kern);
-        } else {
-            run(kern);
-        }
+            }
+        });
     });
     return hipGetLastError();
 }

@@ -683,6 +683,11 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
 }
 
 // ---- push -----------------------------------------------------------------------
+// Waves per SIMD the push is compiled for: in 3D the FP64 state and gather want
+// more registers than four leave (its LDS tile allows three anyway; thermal 128^3,
+// 16.8M: 584 us per step with spills at four, 556 at three).
+template <bool MIX, int DIM> constexpr int push_waves_per_simd() { return (!MIX && DIM == 3) ? 3 : 4; }
+
 // One workgroup per bucket. Wave w takes the units w, w + nw, ... of 64 *
 // lane_parts consecutive slots: each lane loads 16 bytes of every array and
 // writes them back to the same place, whole lines both ways. No slot is
@@ -691,7 +696,7 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
 // the caller's arrays (bucket b from bstart[b]), one by one, and go to the
 // same slots of the pages.
 template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool SCANNED>
-__global__ void __launch_bounds__(kPagePushMax, 4) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
+__global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>())) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
                                                             int64_t n, int64_t max_per, const double *E, const float *E32, PushC pc,
                                                             typename AccOf<MIX>::T *acc, double *part, CtxDev c) {
     static_assert(!EM || (DIM == 2 && VDIM == 3), "the electromagnetic step is 2D3V");
@@ -1211,21 +1216,24 @@ static bool scan_apart(const Geo &g, const PageStep &t, int64_t n, int64_t max_p
     return true;
 }
 
-// Waves per bucket: four, or eight where the buckets leave CUs without a
-// workgroup.
-static int push_block(const Geo &g) { return 2 * g.nbuckets <= cu_count() ? 512 : 256; }
+// Threads per bucket: 256, or twice that with at most two buckets per CU, which
+// leave its SIMDs short of waves. Per step in calls of 20: electromagnetic 8.4M
+// mixed in 512 buckets 175 us with 256 threads, 157 with 512; two-stream 64 x 64,
+// 0.52M mixed in 128 buckets 43.9 us with 256, 38.6 with 512, 40.7 with 1024; but
+// 4.2M mixed between walls in 1024 buckets 73.7 us with 256, 82.8 with 512.
+int push_block(const Geo &g) { return g.nbuckets <= 2 * cu_count() ? kPagePushMax : kBlock; }
 
 hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const Parts *src, const int32_t *bstart,
                             int64_t n, int64_t max_per_bucket, const double *E, const float *E32, const PushC &pc,
                             void *acc, double *part, const CtxDev &c, hipStream_t s) {
-    const dim3 grid(grid_for_buckets(g.nbuckets)), block(push_block(g));
+    const dim3 grid(grid_for_buckets(g.nbuckets));
     const Parts from = src ? *src : Parts{};
     const bool scanned = !src && scan_apart(g, t, n, max_per_bucket, c, s);
     if (g.em) {
         const size_t sh = em_j_tile_bytes(g) + em_f_tile_bytes(g, mixed);
         auto go = [&](auto kern, auto *accp) {
-            hipLaunchKernelGGL(kern, grid, block, sh, s, g, t, from, bstart, n, max_per_bucket, E, nullptr, pc, accp,
-                               part, c);
+            hipLaunchKernelGGL(kern, grid, dim3(push_block(g)), sh, s, g, t, from, bstart, n, max_per_bucket,
+                               E, nullptr, pc, accp, part, c);
         };
         unsigned long long *am = (unsigned long long *)acc;
         double *ad = (double *)acc;
@@ -1244,8 +1252,8 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
     const size_t sh = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
     APIC_DISPATCH(g, mixed, {
         auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, block, sh, s, g, t, from, bstart, n, max_per_bucket, E, MIX ? E32 : nullptr,
-                               pc, (typename AccOf<MIX>::T *)acc, part, c);
+            hipLaunchKernelGGL(kern, grid, dim3(push_block(g)), sh, s, g, t, from, bstart, n,
+                               max_per_bucket, E, MIX ? E32 : nullptr, pc, (typename AccOf<MIX>::T *)acc, part, c);
         };
         // the rotation about z in its own build (in a zero field it is left out)
         auto pick = [&](auto rot) {
