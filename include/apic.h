@@ -300,11 +300,13 @@ apic_status apic_step_static(apic_ctx *ctx, apic_particles *p, void *rho, double
 
 /* Per-phase timing of apic_step with HIP events recorded on the caller's
  * stream around each phase of each step (count pass, scan, push pass, field
- * solve; a step of a call that keeps the particles in pages has no count pass,
- * and its exchange between the buckets is reported as the scan). apic_profile_enable(ctx, max_steps) creates the events (host call,
- * not for capture; max_steps = 0 disables); apic_profile_read waits for the
- * last event and returns the summed milliseconds per phase in ms[4] and the
- * number of profiled steps, then rearms. Steps beyond max_steps are not timed. */
+ * solve; a step of a call that keeps the particles in pages has no count pass
+ * and its push takes the scan along, so both read 0 there; in 1D its push takes
+ * the field solve along too). apic_profile_enable(ctx, max_steps) creates the
+ * events (host call, not for capture; max_steps = 0 disables); apic_profile_read
+ * waits for the last event and returns the summed milliseconds per phase in ms[4]
+ * and the number of profiled steps, then rearms. Steps beyond max_steps are not
+ * timed. */
 apic_status apic_profile_enable(apic_ctx *ctx, int max_steps);
 apic_status apic_profile_read(apic_ctx *ctx, double ms[4], int *steps);
 

@@ -726,7 +726,7 @@ __global__ void __launch_bounds__(kBlock) k_adj_field1d(int nx, double *lE, doub
     extern __shared__ __align__(16) unsigned char smem[];
     double *sr = (double *)smem;
     __shared__ double sRed[kWaves];
-    __shared__ double sScan[kBlock];
+    __shared__ double sScan[2 * kBlock];
     for (int i = threadIdx.x; i < nx; i += blockDim.x) {
         sr[i] = lE[i];
         lE[i] = 0.0;

@@ -225,8 +225,9 @@ PageStep page_step(const apic_ctx *c, void *ws, int k) {
     t.queue = wsp<int32_t>(ws, c->o_pqueue);
     t.head = wsp<unsigned long long>(ws, c->o_phead);
     t.npages = c->npages;
-    int32_t *words = (int32_t *)(t.head + 2);   // three far counters, the live count
+    int32_t *words = (int32_t *)(t.head + 2);   // three far counters, the live count, the buckets done
     t.live = words + 3;
+    t.done = words + 4;
     t.nfar_clear = words + (z + 1) % 3;
     t.pool = wsp<char>(ws, c->o_pool);
     t.out_slots = paged_slots(n);
@@ -369,10 +370,10 @@ apic_status field_from_acc(apic_ctx *c, void *acc, bool acc_is_rho, double *E, f
     const double G = (double)c->d.nx * c->d.ny * c->d.nz;
     if (c->d.dim == 1) {
         const int step_mode = diag ? 1 : 0;
+        const FinArgs fin{diag ? npush : 0, 0, c->mass, c->dV, G, c->d.rho_ion, diag, nullptr, nullptr};
         HIPCHK(c, launch_field1d(c->g, mixed_acc, acc, scale, add, c->d.rho_ion, c->d.lx / c->d.nx, clear, E, E32,
-                                 diag ? diag + 1 : we, diag ? diag + 0 : charge, step_mode, c->d.q_macro, c->dev, s));
-        if (diag && npush)
-            HIPCHK(c, launch_finalize(npush, 0, c->mass, c->dV, G, c->d.rho_ion, diag, nullptr, nullptr, c->dev, s));
+                                 diag ? diag + 1 : we, diag ? diag + 0 : charge, step_mode, c->d.q_macro, fin, c->dev,
+                                 s));
         return APIC_OK;
     }
     double *rho = wsp<double>(ws, c->o_rho);
@@ -792,9 +793,24 @@ apic_status step_paged(apic_ctx *c, apic_particles *p, const Parts &dst, int32_t
         const bool last = k == nsteps - 1;
         hipEvent_t *ev = profile_events(c, true);
         if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
+        PageField f{};
+        if (page_field_folds(c->g) && !(last && rho)) {
+            f.E = E;
+            f.E32 = last ? E32 : nullptr;
+            f.diag = diag;
+            f.scale = acc_scale(c);
+            f.ion = c->d.rho_ion;
+            f.dx = c->d.lx / c->d.nx;
+            f.q_macro = c->d.q_macro;
+            f.mass = c->mass;
+        }
         HIPCHK(c, launch_page_push(c->g, c->mixed, t, k == 0 ? &A : nullptr, p->bucket_start, c->n, max_per_bucket(c),
-                                   E, k > 0 ? e32 : nullptr, pc, acc, diag ? c->dev.part_push : nullptr, c->dev, s));
+                                   E, k > 0 ? e32 : nullptr, pc, acc, diag ? c->dev.part_push : nullptr, f, c->dev, s));
         if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
+        if (f.E) {
+            if (ev && c->prof_all) HIPCHK(c, hipEventRecord(ev[4], s));
+            continue;
+        }
         st = rho_out(c, last ? rho : nullptr, acc, s);
         if (st != APIC_OK) return st;
         st = field_from_acc(c, acc, false, (last || !e32) ? E : nullptr, last ? E32 : e32, diag, nullptr, nullptr,

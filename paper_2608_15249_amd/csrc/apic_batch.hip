@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(kBlock) k_batch(BatchP bp, int32_t *cell, floa
     __shared__ unsigned long long sA[kBatchMaxNx];   // charge; reused as rho for the field solve
     double *sR = reinterpret_cast<double *>(sA);
     __shared__ double sRed[kWaves];
-    __shared__ double sScan[kBlock];
+    __shared__ double sScan[2 * kBlock];
     __shared__ int sItem, sLast, sErr;
     if (threadIdx.x == 0) sErr = 0;
     Parts ps;

@@ -755,40 +755,44 @@ __device__ void flush_region3(typename AccOf<MIX>::T *acc, const typename AccOf<
 // solve of the 3-point Laplacian with centred gradient):
 //   E_{j+1/2} = E_{j-1/2} + (rho_j - <rho>) dx,  sum_j E_{j+1/2} = 0,
 //   E_j = (E_{j-1/2} + E_{j+1/2}) / 2.
-// Whole workgroup (blockDim.x threads, multiple of 64); sr[nx] in LDS holds
-// rho on entry and is overwritten. Returns sum_j E_j^2 and writes E (and E32
-// when non-NULL). The association order of every sum depends only on nx and
-// blockDim.x.
+// Whole workgroup (multiple of 64 threads, kBlock at least); sr[nx] in LDS holds
+// rho on entry and is overwritten, sScan is [2 kBlock]. Returns sum_j E_j^2 and
+// writes E (and E32 when non-NULL). The first kBlock threads do the work whatever
+// the workgroup, so the association order of every sum depends only on nx.
 __device__ double field1d_block(double *sr, int nx, double dx, double *E, float *E32, double *sRed,
                                 double *sScan) {
-    const int T = blockDim.x;
+    constexpr int T = kBlock;
+    const int tid = threadIdx.x;
+    const int i0 = tid < T ? tid : nx;
     double ps = 0.0;
-    for (int i = threadIdx.x; i < nx; i += T) ps += sr[i];
+    for (int i = i0; i < nx; i += T) ps += sr[i];
     const double mean = block_sum(ps, sRed) / (double)nx;
     const int per = (nx + T - 1) / T;
-    const int lo = threadIdx.x * per, hi = min(nx, lo + per);
+    const int lo = min(nx, tid * per), hi = min(nx, lo + per);
     double loc = 0.0;
     for (int i = lo; i < hi; ++i) loc += (sr[i] - mean) * dx;
-    sScan[threadIdx.x] = loc;
+    double incl = loc;
+    if (tid < T) sScan[tid] = incl;
     __syncthreads();
-    for (int off = 1; off < T; off <<= 1) {
-        double addv = (threadIdx.x >= (unsigned)off) ? sScan[threadIdx.x - off] : 0.0;
-        __syncthreads();
-        sScan[threadIdx.x] += addv;
+    // two buffers in turn: one barrier per round
+    for (int off = 1, at = 0; off < T; off <<= 1, at ^= 1) {
+        if (tid < T) {
+            incl += tid >= off ? sScan[at * T + tid - off] : 0.0;
+            sScan[(at ^ 1) * T + tid] = incl;
+        }
         __syncthreads();
     }
-    double run = sScan[threadIdx.x] - loc;
-    __syncthreads();
+    double run = incl - loc;
     for (int i = lo; i < hi; ++i) {
         run += (sr[i] - mean) * dx;
         sr[i] = run;                       // E_{i+1/2} up to a constant
     }
     __syncthreads();
     double hs = 0.0;
-    for (int i = threadIdx.x; i < nx; i += T) hs += sr[i];
+    for (int i = i0; i < nx; i += T) hs += sr[i];
     const double hmean = block_sum(hs, sRed) / (double)nx;
     double wpart = 0.0;
-    for (int i = threadIdx.x; i < nx; i += T) {
+    for (int i = i0; i < nx; i += T) {
         const int im = (i == 0) ? nx - 1 : i - 1;
         const double e = 0.5 * ((sr[im] - hmean) + (sr[i] - hmean));
         E[i] = e;

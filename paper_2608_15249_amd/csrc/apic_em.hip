@@ -379,7 +379,7 @@ static apic_status em_step_paged(apic_ctx *c, apic_particles *p, double *F, doub
         hipEvent_t *ev = profile_events(c, true);
         if (ev) HIPCHK(c, hipEventRecord(ev[2], s));
         HIPCHK(c, launch_page_push(c->g, c->mixed, t, k == 0 ? &A : nullptr, p->bucket_start, c->n, max_per_bucket(c),
-                                   Fk, nullptr, pc, Jk, diag ? c->dev.part_push : nullptr, c->dev, s));
+                                   Fk, nullptr, pc, Jk, diag ? c->dev.part_push : nullptr, PageField{}, c->dev, s));
         if (ev) HIPCHK(c, hipEventRecord(ev[3], s));
         HIPCHK(c, launch_fdtd_step(c->g, Fk, Fk1, Jk, Jk1, (J && last) ? J : nullptr, c->d.dt, c2, c->d.bz, c->dV,
                                    c->mass, nb, diag, c->dev, s));

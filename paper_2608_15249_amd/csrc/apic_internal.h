@@ -208,11 +208,10 @@ int fused_fft3_spec_blocks(const Geo &g);
 hipError_t launch_fused_field3(const Geo &g, bool mixed_acc, void *acc, double scale, double add, int clear,
                                void *A, void *B, double *phi, const double *tw, unsigned long long *qacc,
                                const CtxDev &c, hipStream_t s);
-hipError_t launch_finalize(int npush, int nspec, double mass, double dV, double G, double rho_ion,
-                           double *diag, double *we, double *charge, const CtxDev &c, hipStream_t s);
 hipError_t launch_field1d(const Geo &g, bool mixed, void *acc, double scale, double add, double ion,
                           double dx, int clear, double *E, float *E32, double *we_out,
-                          double *charge_out, int step_mode, double q_macro, const CtxDev &c, hipStream_t s);
+                          double *charge_out, int step_mode, double q_macro, const FinArgs &fin, const CtxDev &c,
+                          hipStream_t s);
 
 // ---- electromagnetic step (FP64 2D3V, Yee grid; F = [6][G], J = [3][G]) ----
 // F^0 from the potential phi [G]: (Ex, Ey) = -(forward differences of phi),

@@ -1153,8 +1153,6 @@ __global__ void __launch_bounds__(kBlock) k_rho_odd(Geo g, typename AccOf<MIX>::
     }
 }
 
-__global__ void __launch_bounds__(1024) k_finalize(FinArgs f, CtxDev c) { finalize_block(f, c); }
-
 // phi_hat = rho_hat / K^2 (K^2 = sum of the per-axis modified wavenumbers,
 // phi_hat(0) = 0), scaled by 1/G for the unnormalised inverse transform, and
 // the per-block partials of sum |E_hat|^2 = sum kappa^2 |phi_hat|^2 over the
@@ -1264,18 +1262,24 @@ __global__ void __launch_bounds__(kBlock) k_grad(Geo g, const double *__restrict
 //   W_E      = 0.5 * dV / G * sum(part_spec)      (Parseval)
 //   charge   = dV * (rho0 - G * rho_ion)
 
-// 1D field (one workgroup of kBlock threads; nodes held in LDS).
+// 1D field (one workgroup of kBlock threads; nodes held in LDS). The kinetic
+// diagnostics of the step are the work of a second workgroup where fin.npush is
+// set (a launch of their own took 4.5 us).
 // Fixed-point sums (MIX): the charge is their exact integer total (sd = S
 // weight bits per particle) times q_macro, also stored in c.qexact.
 template <bool MIX>
 __global__ void __launch_bounds__(kBlock) k_field1d(int nx, typename AccOf<MIX>::T *acc, double scale,
                                                     double add, double ion, double dx, int clear, double *E,
                                                     float *E32, double *we, double *charge, int step_mode,
-                                                    int sd, double q_macro, CtxDev c) {
+                                                    int sd, double q_macro, FinArgs fin, CtxDev c) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sr = (double *)smem;          // [nx] rho, then half-node field
     __shared__ double sRed[kWaves];
-    __shared__ double sScan[kBlock];
+    __shared__ double sScan[2 * kBlock];
+    if (blockIdx.x == 1) {
+        finalize_block(fin, c);
+        return;
+    }
     double part = 0.0;
     QSum q{0, 0};
     for (int i = threadIdx.x; i < nx; i += blockDim.x) {
@@ -1541,23 +1545,17 @@ hipError_t launch_grad(const Geo &g, const double *phi, double *E, float *E32, c
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(int npush, int nspec, double mass, double dV, double G, double rho_ion, double *diag,
-                           double *we, double *charge, const CtxDev &c, hipStream_t s) {
-    const FinArgs f{npush, nspec, mass, dV, G, rho_ion, diag, we, charge};
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, s, f, c);
-    return hipGetLastError();
-}
-
 hipError_t launch_field1d(const Geo &g, bool mixed, void *acc, double scale, double add, double ion, double dx,
                           int clear, double *E, float *E32, double *we_out, double *charge_out, int step_mode,
-                          double q_macro, const CtxDev &c, hipStream_t s) {
+                          double q_macro, const FinArgs &fin, const CtxDev &c, hipStream_t s) {
     size_t sh = (size_t)g.nx * sizeof(double);
+    const dim3 grid(fin.npush ? 2 : 1);
     if (mixed)
-        hipLaunchKernelGGL(k_field1d<true>, dim3(1), dim3(kBlock), sh, s, g.nx, (unsigned long long *)acc, scale, add,
-                           ion, dx, clear, E, E32, we_out, charge_out, step_mode, g.S * g.dim, q_macro, c);
+        hipLaunchKernelGGL(k_field1d<true>, grid, dim3(kBlock), sh, s, g.nx, (unsigned long long *)acc, scale, add,
+                           ion, dx, clear, E, E32, we_out, charge_out, step_mode, g.S * g.dim, q_macro, fin, c);
     else
-        hipLaunchKernelGGL(k_field1d<false>, dim3(1), dim3(kBlock), sh, s, g.nx, (double *)acc, scale, add, ion, dx,
-                           clear, E, E32, we_out, charge_out, step_mode, 0, q_macro, c);
+        hipLaunchKernelGGL(k_field1d<false>, grid, dim3(kBlock), sh, s, g.nx, (double *)acc, scale, add, ion, dx,
+                           clear, E, E32, we_out, charge_out, step_mode, 0, q_macro, fin, c);
     return hipGetLastError();
 }
 

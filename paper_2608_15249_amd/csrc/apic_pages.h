@@ -43,11 +43,25 @@ struct PageStep {
     unsigned long long *head;        // [2] pages taken from and given to the ring so far
     int64_t npages;
     int32_t *live;                   // [1] particles not absorbed by a wall
+    int32_t *done;                   // [1] buckets whose 1D push has ended, zero between the steps
     int32_t *nfar_clear;             // [1] the next step's PageList::nfar
     char *pool;                      // [npages] pages
     int64_t out_slots;               // n rounded up
     PageList in, to;                 // leavers of the step before, of this one
 };
+
+// The 1D field solve inside the push (E set): the workgroup that ends last solves
+// it, with the step's diagnostics, from the charge that all have added.
+struct PageField {
+    double *E;
+    float *E32;                       // or NULL
+    double *diag;                     // or NULL
+    double scale, ion, dx, q_macro, mass;
+};
+
+// Whether the push can take the field solve along: 1D, the nodes held in LDS
+// beside the workgroups of a whole chip.
+inline bool page_field_folds(const Geo &g) { return g.dim == 1 && g.nx <= 2048; }
 
 hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int32_t *nfar3, int64_t n,
                              int64_t max_per_bucket, const int32_t *bstart, uint64_t *acc, int64_t nacc,
@@ -55,7 +69,7 @@ hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int
 // src: the caller's arrays (with bstart) in a call's first step, else NULL
 hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const Parts *src, const int32_t *bstart,
                             int64_t n, int64_t max_per_bucket, const double *E, const float *E32, const PushC &pc,
-                            void *acc, double *part, const CtxDev &c, hipStream_t s);
+                            void *acc, double *part, const PageField &f, const CtxDev &c, hipStream_t s);
 hipError_t launch_page_end(const Geo &g, bool mixed, const PageStep &t, int64_t n, int64_t max_per_bucket,
                            const Parts &dst, int32_t *bstart, const CtxDev &c, hipStream_t s);
 

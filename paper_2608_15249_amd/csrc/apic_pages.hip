@@ -10,14 +10,13 @@
 // and writes it back to the same addresses, and only the leavers are copied
 // out and dealt to their new buckets:
 //
-//   k_page_push      per bucket: gather, advance, move, deposit, the whole
-//                    state written back in place; then the leavers, ordered
-//                    by direction, are copied to the bucket's part of an
-//                    outbox and their slots listed as holes
-//   k_page_exchange  per bucket: arrivals from the neighbours' outboxes fill
-//                    the bucket's holes, further ones are appended (pages
-//                    taken from a queue of free ones), holes left over are
-//                    filled from the bucket's end (pages given back)
+//   k_page_push  per bucket: first the exchange of the step before (arrivals
+//                from the neighbours' outboxes fill the bucket's holes, further
+//                ones are appended with pages from a queue of free ones, holes
+//                left over are filled from the bucket's end and pages given
+//                back); then gather, advance, move, deposit, the whole state
+//                written back in place, the leavers copied to the bucket's part
+//                of an outbox and listed by direction, their slots as holes
 //
 // A call starts with k_page_scan and k_page_fill (bucket counts, page table),
 // its first push reads the caller's arrays and writes the pages, and it ends
@@ -28,10 +27,10 @@
 // and which page a bucket gets from the queue decides no result.
 //
 // Magnetized 2D3V, 1024 x 1024 cells, 33.5M mixed particles, 32 x 16 tiles: the
-// reordering step's count, scan and push took 16 + 6 + 418 us, the push and the
-// exchange here 342 + 19 us (1.61 GB of state read and written: 4.7 TB/s, where
-// a copy of 1 GB on the same card runs at 5.07 TB/s and the push's own page
-// traffic without any arithmetic took 331 us).
+// reordering step's count, scan and push took 16 + 6 + 418 us, the push with its
+// exchange 364 us (1.61 GB of state read and written: 4.4 TB/s, where a copy of
+// 1 GB on the same card runs at 5.07 TB/s and the push's own page traffic without
+// any arithmetic took 331 us).
 #include <algorithm>
 #include <type_traits>
 
@@ -136,6 +135,7 @@ __global__ void __launch_bounds__(kBlock) k_page_fill(int nb, PageStep t, int32_
         t.head[1] = (unsigned long long)(t.npages - used);
         for (int i = 0; i < 3; ++i) nfar3[i] = 0;
         *t.live = t.ds[nb];
+        *t.done = 0;
     }
 }
 
@@ -688,6 +688,71 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
 // 16.8M: 584 us per step with spills at four, 556 at three).
 template <bool MIX, int DIM> constexpr int push_waves_per_simd() { return (!MIX && DIM == 3) ? 3 : 4; }
 
+// The end of a 1D push: the workgroup that ends last solves the field of the
+// charge that all have added and leaves the sums at zero for the next step.
+// (What the others wrote and this one reads, the sums, the partials and the step,
+// passes through device-scope atomics; each thread waits for its own, the barrier
+// for everyone's, before the workgroup is counted. No workgroup waits for
+// another.) The solve and its diagnostics were launches
+// of their own: 64 nodes, 16384 particles in 4 buckets 27.0 us per step in calls
+// of 20, 23.5 with the solve here (FP64 27.0 and 22.9).
+template <bool MIX>
+__device__ void field_by_last(const Geo &g, const PageStep &t, const PageField &f, typename AccOf<MIX>::T *acc,
+                              const double *part, unsigned char *smem, const CtxDev &c) {
+    using A = typename AccOf<MIX>::T;
+    __shared__ double sRed[kPagePushMax / 64];
+    __shared__ int sLast;
+    double *sr = (double *)smem, *sScan = sr + g.nx;
+    __builtin_amdgcn_s_waitcnt(kWaitVmem);
+    __syncthreads();
+    if (threadIdx.x == 0) sLast = atomicAdd(t.done, 1) == g.nbuckets - 1;
+    __syncthreads();
+    if (!sLast) return;
+    const int sd = g.S * g.dim;
+    double tot = 0.0;
+    QSum q{0, 0};
+    for (int i = threadIdx.x < kBlock ? threadIdx.x : g.nx; i < g.nx; i += kBlock) {
+        double w;
+        if constexpr (MIX) {
+            const int64_t v = (int64_t)atomicExch(&acc[i], (A)0);
+            w = (double)v;
+            qsum_add(q, v, sd);
+        } else {
+            w = __longlong_as_double((long long)atomicExch((unsigned long long *)&acc[i], 0ull));
+        }
+        const double r = f.ion + f.scale * w;
+        sr[i] = r;
+        tot += r - f.ion;
+    }
+    double charge = block_sum(tot, sRed) * f.dx;
+    if constexpr (MIX) {
+        const QSum qt = qsum_block(q, sd);
+        if (threadIdx.x == 0) {
+            c.qexact[0] = qt.whole;
+            c.qexact[1] = (int64_t)qt.rem;
+            charge = qsum_charge(qt, sd, f.q_macro);
+        }
+    }
+    const double wsum = field1d_block(sr, g.nx, f.dx, f.E, f.E32, sRed, sScan);
+    if (f.diag) {
+        double k = 0.0, p = 0.0;
+        for (int i = threadIdx.x; i < g.nbuckets; i += blockDim.x) {
+            k += __hip_atomic_load(&part[2 * i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            p += __hip_atomic_load(&part[2 * i + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        k = block_sum(k, sRed);
+        p = block_sum(p, sRed);
+        if (threadIdx.x == 0) {
+            double *d = f.diag + 4 * __hip_atomic_load(c.step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            d[0] = charge;
+            d[1] = 0.5 * wsum * f.dx;
+            d[2] = 0.5 * f.mass * k;
+            d[3] = f.mass * p;
+        }
+    }
+    if (threadIdx.x == 0) *t.done = 0;
+}
+
 // One workgroup per bucket. Wave w takes the units w, w + nw, ... of 64 *
 // lane_parts consecutive slots: each lane loads 16 bytes of every array and
 // writes them back to the same place, whole lines both ways. No slot is
@@ -698,7 +763,7 @@ template <bool MIX, int DIM> constexpr int push_waves_per_simd() { return (!MIX 
 template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool SCANNED>
 __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>())) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
                                                             int64_t n, int64_t max_per, const double *E, const float *E32, PushC pc,
-                                                            typename AccOf<MIX>::T *acc, double *part, CtxDev c) {
+                                                            typename AccOf<MIX>::T *acc, double *part, PageField f, CtxDev c) {
     static_assert(!EM || (DIM == 2 && VDIM == 3), "the electromagnetic step is 2D3V");
     using R = typename Pt<MIX>::R;
     using A = typename AccOf<MIX>::T;
@@ -729,7 +794,8 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
     const int b = bucket_of_block(g.nbuckets);
     if (b >= g.nbuckets) return;
     if (b == 0 && threadIdx.x == 0) {
-        *c.step = *c.step + 1;
+        // (the workgroup that solves the 1D field reads the step in this launch)
+        __hip_atomic_store(c.step, *c.step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *t.nfar_clear = 0;
     }
     if constexpr (!FIRST) {
@@ -1092,8 +1158,8 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                     kt += sKe[w2];
                     pt += sPx[w2];
                 }
-                part[2 * b] = 0.5 * kt;
-                part[2 * b + 1] = pt;
+                __hip_atomic_store(&part[2 * b], 0.5 * kt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&part[2 * b + 1], pt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (count > nout) atomicAdd(&t.cnt_next[b], count - nout);
         }
@@ -1153,6 +1219,9 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
     }
     __syncthreads();
     if (threadIdx.x == 0 && sErr) raise_err(c.err, sErr);
+    if constexpr (DIM == 1) {
+        if (f.E) field_by_last<MIX>(g, t, f, acc, part, smem, c);
+    }
 }
 
 // ---- back to the caller's arrays --------------------------------------------------
@@ -1225,7 +1294,7 @@ int push_block(const Geo &g) { return g.nbuckets <= 2 * cu_count() ? kPagePushMa
 
 hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const Parts *src, const int32_t *bstart,
                             int64_t n, int64_t max_per_bucket, const double *E, const float *E32, const PushC &pc,
-                            void *acc, double *part, const CtxDev &c, hipStream_t s) {
+                            void *acc, double *part, const PageField &f, const CtxDev &c, hipStream_t s) {
     const dim3 grid(grid_for_buckets(g.nbuckets));
     const Parts from = src ? *src : Parts{};
     const bool scanned = !src && scan_apart(g, t, n, max_per_bucket, c, s);
@@ -1233,7 +1302,7 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         const size_t sh = em_j_tile_bytes(g) + em_f_tile_bytes(g, mixed);
         auto go = [&](auto kern, auto *accp) {
             hipLaunchKernelGGL(kern, grid, dim3(push_block(g)), sh, s, g, t, from, bstart, n, max_per_bucket,
-                               E, nullptr, pc, accp, part, c);
+                               E, nullptr, pc, accp, part, f, c);
         };
         unsigned long long *am = (unsigned long long *)acc;
         double *ad = (double *)acc;
@@ -1249,11 +1318,12 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         else pick(std::false_type{}, std::false_type{});
         return hipGetLastError();
     }
-    const size_t sh = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
+    const size_t tile = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
+    const size_t sh = f.E ? std::max(tile, (size_t)(g.nx + 2 * kBlock) * sizeof(double)) : tile;
     APIC_DISPATCH(g, mixed, {
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, grid, dim3(push_block(g)), sh, s, g, t, from, bstart, n,
-                               max_per_bucket, E, MIX ? E32 : nullptr, pc, (typename AccOf<MIX>::T *)acc, part, c);
+                               max_per_bucket, E, MIX ? E32 : nullptr, pc, (typename AccOf<MIX>::T *)acc, part, f, c);
         };
         // the rotation about z in its own build (in a zero field it is left out)
         auto pick = [&](auto rot) {
