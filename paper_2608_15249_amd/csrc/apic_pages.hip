@@ -41,6 +41,7 @@ namespace apic {
 
 namespace {
 
+constexpr int64_t kPageCached = int64_t(208) << 20;   // bytes of particles that stay in the caches between steps
 constexpr int kPageScanMax = 4096;   // buckets up to which the exchange scans the counts itself
 
 // ---- page table of a call ------------------------------------------------------
@@ -158,9 +159,7 @@ template <bool MIX, int DIM, int VDIM> struct Rec {
 template <typename T, int K, int OFF>
 constexpr int piece() { return (sizeof(T) == 4 && K - OFF >= 4) ? 4 : (K - OFF >= 2) ? 2 : 1; }
 
-// NT: the nontemporal hint, for whole pages, each read and written once per step
-// (the push at 1024 x 1024, 33.5M mixed 2D3V particles, took 421 us with cached
-// stores and 358 us with the hint).
+// NT: the nontemporal hint, for whole pages, each read and written once per step.
 template <bool NT, typename T, int K, int OFF = 0>
 __device__ __forceinline__ void load_words(const char *base, int64_t slots, unsigned i, T *w) {
     constexpr int N = piece<T, K, OFF>();
@@ -760,7 +759,7 @@ __device__ void field_by_last(const Geo &g, const PageStep &t, const PageField &
 // leavers to its own part of the bucket's list. FIRST: the particles come from
 // the caller's arrays (bucket b from bstart[b]), one by one, and go to the
 // same slots of the pages.
-template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool SCANNED>
+template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool SCANNED, bool NT>
 __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>())) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
                                                             int64_t n, int64_t max_per, const double *E, const float *E32, PushC pc,
                                                             typename AccOf<MIX>::T *acc, double *part, PageField f, CtxDev c) {
@@ -837,7 +836,7 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                     read_array<MIX, DIM, VDIM>(src, i0 + min((w + i * nw) * kPage + j * 64 + lane, count - 1), r[j]);
             } else {
 #pragma unroll
-                for (int j = 0; j < U; ++j) load_slot<MIX, DIM, VDIM>(s, j * 64 + lane, r[j]);
+                for (int j = 0; j < U; ++j) load_slot<MIX, DIM, VDIM, NT>(s, j * 64 + lane, r[j]);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -955,7 +954,7 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                 }
             }
 #pragma unroll
-            for (int j = 0; j < U; ++j) store_slot<MIX, DIM, VDIM>(s, j * 64 + lane, r[j]);
+            for (int j = 0; j < U; ++j) store_slot<MIX, DIM, VDIM, NT>(s, j * 64 + lane, r[j]);
         };
         // a unit of a later step: groups of kGroup particles in straight-line code
         constexpr int kGroup = (MIX && DIM < 3) ? U : 1;
@@ -1114,7 +1113,7 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                 }
             }
 #pragma unroll
-            for (int j = 0; j < U; ++j) store_slot<MIX, DIM, VDIM>(s, j * 64 + lane, r[j]);
+            for (int j = 0; j < U; ++j) store_slot<MIX, DIM, VDIM, NT>(s, j * 64 + lane, r[j]);
         };
         // (the caller's arrays take the form that checks its input, and the
         // electromagnetic step its own)
@@ -1308,16 +1307,25 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         double *ad = (double *)acc;
         auto pick = [&](auto first, auto sc) {
             constexpr bool F = decltype(first)::value, S = decltype(sc)::value;
-            if (mixed && g.hc) go(k_page_push<true, 2, 3, true, true, false, F, S>, am);
-            else if (mixed) go(k_page_push<true, 2, 3, false, true, false, F, S>, am);
-            else if (g.hc) go(k_page_push<false, 2, 3, true, true, false, F, S>, ad);
-            else go(k_page_push<false, 2, 3, false, true, false, F, S>, ad);
+            if (mixed && g.hc) go(k_page_push<true, 2, 3, true, true, false, F, S, true>, am);
+            else if (mixed) go(k_page_push<true, 2, 3, false, true, false, F, S, true>, am);
+            else if (g.hc) go(k_page_push<false, 2, 3, true, true, false, F, S, true>, ad);
+            else go(k_page_push<false, 2, 3, false, true, false, F, S, true>, ad);
         };
         if (src) pick(std::true_type{}, std::false_type{});
         else if (scanned) pick(std::false_type{}, std::true_type{});
         else pick(std::false_type{}, std::false_type{});
         return hipGetLastError();
     }
+    // Below 3D, pages that the memory-side cache (256 MB) can hold from step to step
+    // go through the caches, others past them with the nontemporal hint. Per step in
+    // calls of 20 with the hint and without: 2D2V FP64 128 MB 94.9 and 86.0 us, 208 MB
+    // 141 and 135, 288 MB 202 and 214, 537 MB 288 and 339; 2D3V mixed 144 MB 111 and
+    // 100, 216 MB 163 and 157, 288 MB 186 and 197; walls 160 MB 126 and 122, 240 MB
+    // 184 and 189. 3D mixed 56 MB 173 and 170, 168 MB 225 and 230, 470 MB 384 and 431.
+    // (The electromagnetic push is not bound by its pages: 201 MB 156 and 158.)
+    const int64_t state = n * (mixed ? 4 * (1 + g.dim + g.vdim) : 8 * (g.dim + g.vdim));
+    const bool cached = state <= kPageCached;
     const size_t tile = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
     const size_t sh = f.E ? std::max(tile, (size_t)(g.nx + 2 * kBlock) * sizeof(double)) : tile;
     APIC_DISPATCH(g, mixed, {
@@ -1328,11 +1336,18 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         // the rotation about z in its own build (in a zero field it is left out)
         auto pick = [&](auto rot) {
             constexpr bool ROT = decltype(rot)::value;
-            if (scanned) go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true>);
-            else go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false>);
+            if constexpr (DIM < 3) {
+                if (cached) {
+                    if (scanned) go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true, false>);
+                    else go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false, false>);
+                    return;
+                }
+            }
+            if (scanned) go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true, true>);
+            else go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false, true>);
         };
         if (src) {
-            go(k_page_push<MIX, DIM, VDIM, HC, false, false, true, false>);
+            go(k_page_push<MIX, DIM, VDIM, HC, false, false, true, false, true>);
         } else if constexpr (VDIM >= 2 && !HC) {
             if (pc.t != 0.0) pick(std::true_type{});
             else pick(std::false_type{});
