@@ -379,12 +379,16 @@ apic_status field_from_acc(apic_ctx *c, void *acc, bool acc_is_rho, double *E, f
     double *rho = wsp<double>(ws, c->o_rho);
     void *rhat = wsp<void>(ws, c->o_rhat);
     char *ehat = wsp<char>(ws, c->o_ehat);
-    if (c->fused_fft) {
+    if (c->fused_fft || c->dft_field) {
         // half spectra in rhat, the x-spectrum of Ex + i Ey ([ny][nx] complex) in ehat
         const FinArgs fin{diag ? npush : 0, 0, c->mass, c->dV, G, c->d.rho_ion, diag, we, charge, c->g.walls,
                           c->d.q_macro, nlive, mixed_acc ? c->g.S * c->d.dim : 0};
-        HIPCHK(c, launch_fused_field(c->g, mixed_acc, acc, scale, add, clear, rhat, ehat, E, E32, c->dev.tw, fin,
-                                     c->dev, s));
+        if (c->fused_fft)
+            HIPCHK(c, launch_fused_field(c->g, mixed_acc, acc, scale, add, clear, rhat, ehat, E, E32, c->dev.tw, fin,
+                                         c->dev, s));
+        else
+            HIPCHK(c, launch_dft_field(c->g, mixed_acc, acc, scale, add, clear, rhat, ehat, E, E32, c->dft, fin,
+                                       c->dev, s));
         return APIC_OK;
     }
     if (c->fused_fft3) {
@@ -588,8 +592,11 @@ apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ct
     const bool lib_fft = fft_env && std::string(fft_env) == "library";
     c->fused_fft = fused_fft_supported(d.dim, g.nx, g.ny, g.nz) && !lib_fft;
     c->fused_fft3 = fused_fft3_supported(d.dim, g.nx, g.ny, g.nz) && !lib_fft;
+    c->dft_field = !c->fused_fft && dft_field_supported(d.dim, g.nx, g.ny) && !lib_fft;
     const int nmax = std::max(g.nx, std::max(g.ny, d.dim == 3 ? g.nz : 1));
-    const size_t tw_bytes = (c->fused_fft || c->fused_fft3) ? 2 * sizeof(double) * nmax : 0;   // nmax complex
+    // nmax complex, or those of both sides
+    const int ntw = (c->fused_fft || c->fused_fft3) ? nmax : c->dft_field ? g.nx + g.ny : 0;
+    const size_t tw_bytes = 2 * sizeof(double) * ntw;
     size_t bytes = align256(sizeof(int)) * 2 + align256(sizeof(double) * 2 * g.nbuckets) +
                    align256(sizeof(double) * kMaxSpecBlocks) + align256(sizeof(double)) +
                    align256(sizeof(double) * hx) * 2 + align256(sizeof(double) * g.ny) * 2 +
@@ -612,6 +619,7 @@ apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ct
     c->dev.kz2 = (double *)take(sizeof(double) * g.nz);
     c->dev.kapz = (double *)take(sizeof(double) * g.nz);
     c->dev.tw = tw_bytes ? (double *)take(tw_bytes) : nullptr;
+    if (c->dft_field) c->dft = dft_plan_of(g.nx, g.ny, c->dev.tw);
     {
         int64_t *q = (int64_t *)take(((size_t)kQSlots * kQStride + 2) * sizeof(int64_t));
         c->dev.qacc = (unsigned long long *)q;
@@ -647,12 +655,14 @@ apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ct
                   hipMemcpy(c->dev.kz2, kz2.data(), sizeof(double) * g.nz, hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->dev.kapz, kapz.data(), sizeof(double) * g.nz, hipMemcpyHostToDevice) == hipSuccess;
     if (copied && tw_bytes) {
-        // exp(-2 pi i k / nmax), k < nmax; the angle 2 pi k / nmax is one rounding of pi times an exact ratio
-        std::vector<double> tw(2 * nmax);
-        for (int k = 0; k < nmax; ++k) {
-            const double ang = M_PI * (2.0 * k / nmax);
-            tw[2 * k] = std::cos(ang);
-            tw[2 * k + 1] = -std::sin(ang);
+        // exp(-2 pi i k / n), k < n; the angle 2 pi k / n is one rounding of pi times an exact ratio
+        std::vector<double> tw(2 * ntw);
+        for (int i = 0; i < ntw; ++i) {
+            const int n = !c->dft_field ? nmax : i < g.nx ? g.nx : g.ny;
+            const int k = c->dft_field && i >= g.nx ? i - g.nx : i;
+            const double ang = M_PI * (2.0 * k / n);
+            tw[2 * i] = std::cos(ang);
+            tw[2 * i + 1] = -std::sin(ang);
         }
         copied = hipMemcpy(c->dev.tw, tw.data(), tw_bytes, hipMemcpyHostToDevice) == hipSuccess;
     }

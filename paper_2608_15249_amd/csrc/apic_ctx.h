@@ -22,6 +22,8 @@ struct apic_ctx {
     hipfftHandle fwd = 0, inv = 0;
     bool have_fft = false;
     bool fused_fft = false;   // 2D periodic field solve by the fused three-launch path
+    bool dft_field = false;   // the same on other 2D grids, lines of any length
+    apic::DftPlan dft{};
     bool fused_fft3 = false;  // 3D periodic field solve by the fused transforms in LDS
     std::string err;
     // workspace layout (byte offsets)

@@ -195,6 +195,25 @@ bool fused_fft_supported(int dim, int nx, int ny, int nz);
 hipError_t launch_fused_field(const Geo &g, bool mixed_acc, void *acc, double scale, double add, int clear,
                               void *H, void *Z, double *E, float *E32, const double *tw, const FinArgs &f,
                               const CtxDev &c, hipStream_t s);
+// The same on other 2D grids (apic_dft.hip): sides up to kDftMax whose factors
+// keep the sums of a line short. tw: the roots of unity exp(-2 pi i j / n), nx of them, then
+// ny.
+constexpr int kDftMax = 1024;
+constexpr int kDftPasses = 4;      // factors of a side, at most
+constexpr int kDftBlock = 512;     // threads per line, at most
+struct DftLine {
+    int n, passes;
+    int p[kDftPasses];
+};
+struct DftPlan {
+    DftLine x, y;
+    const double *tw;
+};
+bool dft_field_supported(int dim, int nx, int ny);
+DftPlan dft_plan_of(int nx, int ny, const double *tw);
+hipError_t launch_dft_field(const Geo &g, bool mixed_acc, void *acc, double scale, double add, int clear, void *H,
+                            void *Z, double *E, float *E32, const DftPlan &p, const FinArgs &f, const CtxDev &c,
+                            hipStream_t s);
 // Fused periodic 3D field solve (apic_fft3.hip): power-of-two nx, ny, nz in
 // [4, kFusedFft3Max]. acc -> rho (acc cleared when clear; with qacc, the
 // fixed-point node sums' exact total is added to it) -> phi (FP64 [G]) with
