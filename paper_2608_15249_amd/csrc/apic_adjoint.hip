@@ -941,6 +941,11 @@ apic_status adj_solve(apic_ctx *c, double *lE, double *lrho, char *ws_ctx, hipSt
         HIPCHK(c, hipGetLastError());
         return APIC_OK;
     }
+    if (c->fused_fft || c->dft_field) {
+        HIPCHK(c, launch_adj_field(c->g, c->fused_fft, lE, wsp<char>(ws_ctx, c->o_ehat), wsp<char>(ws_ctx, c->o_rhat),
+                                   lrho, c->dev.tw, c->dft, c->dev, s));
+        return APIC_OK;
+    }
     // half spectra of the dim components (the context's one rho spectrum and
     // its dim phi spectra hold them), combined in place into the first
     const size_t H = (size_t)(c->d.nx / 2 + 1) * c->d.ny * c->d.nz;

@@ -214,6 +214,11 @@ DftPlan dft_plan_of(int nx, int ny, const double *tw);
 hipError_t launch_dft_field(const Geo &g, bool mixed_acc, void *acc, double scale, double add, int clear, void *H,
                             void *Z, double *E, float *E32, const DftPlan &p, const FinArgs &f, const CtxDev &c,
                             hipStream_t s);
+// lam_rho = A^T lam_E, the adjoint of the 2D solve (apic_adjfield.hip), through the
+// same transforms; lE [2][G] is zero afterwards. Z: [ny][nx] complex, H:
+// [ny][nx/2+1] complex scratch. Power-of-two sides with tw, others with p.
+hipError_t launch_adj_field(const Geo &g, bool pow2, double *lE, void *Z, void *H, double *lrho, const double *tw,
+                            const DftPlan &p, const CtxDev &c, hipStream_t s);
 // Fused periodic 3D field solve (apic_fft3.hip): power-of-two nx, ny, nz in
 // [4, kFusedFft3Max]. acc -> rho (acc cleared when clear; with qacc, the
 // fixed-point node sums' exact total is added to it) -> phi (FP64 [G]) with
