@@ -25,7 +25,7 @@
 //   workgroup reduces the diagnostics.
 // The mathematics of the general path (library real-to-complex transforms,
 // spectral division, real-space centred difference) with the transforms
-// done in LDS; every global read and write covers runs of at least 128
+// done in LDS; every global read and write covers runs of at least 64
 // bytes.
 #include "apic_fftlds.h"
 
@@ -40,12 +40,14 @@ struct Split3 {
 
 inline Split3 split3(const Geo &g) {
     Split3 s;
-    s.Y = g.nx <= 128 ? 16 : 8;
+    // small workgroups, several to a CU, so that the loads of some overlap the passes
+    // of others (64-byte runs in the y launches; solve and gradient at 128^3 / 32^3 in
+    // us: 85.7 / 26.4 with 16 rows, 8 planes, 8 ky, 83.2 / 24.4 with 8, 4, 4; 89.6 with
+    // 32 rows, 90.6 with 16 planes, 89.3 with 16 ky, 93.4 with 2)
+    s.Y = 8;
     if (s.Y > g.ny) s.Y = g.ny;
-    s.ZB = g.nz < 8 ? g.nz : 8;
-    // (the z workgroup also holds a small reduction array: 2 KY nz complex
-    // stay below 64 KiB)
-    s.KY = g.nz <= 128 ? 8 : 4;
+    s.ZB = g.nz <= 128 ? 4 : 8;
+    s.KY = 4;
     if (s.KY > g.ny) s.KY = g.ny;
     return s;
 }

@@ -1194,7 +1194,10 @@ __global__ void __launch_bounds__(kBlock) k_spectral(Geo g, const double2 *rh, d
 // its binary32 rounding. h = 1 / (2 d) per axis.
 // The last workgroup of the launch reduces the field diagnostics instead
 // (it reads only what earlier launches wrote).
-template <int DIM>
+// PAIR: nx even, E and E32 aligned to a pair. Bound by the stores of E: 128^3, E32
+// written, 22.4 us with one node per lane and the rows dealt to the XCDs in turn,
+// 17.4 with pairs and each XCD's rows adjacent.
+template <int DIM, bool PAIR>
 __global__ void __launch_bounds__(kBlock) k_grad(Geo g, const double *__restrict__ phi, double *__restrict__ E,
                                                  float *__restrict__ E32, double hx, double hy, double hz, FinArgs f,
                                                  CtxDev c) {
@@ -1205,51 +1208,83 @@ __global__ void __launch_bounds__(kBlock) k_grad(Geo g, const double *__restrict
     const int64_t G = (int64_t)g.nx * g.ny * g.nz;
     const int64_t sxy = (int64_t)g.nx * g.ny;
     const int64_t rows = (int64_t)g.ny * g.nz;
-    // one (y, z) row per wave at a time: the neighbour rows' offsets once per row
+    // one (y, z) row per wave at a time: the neighbour rows' offsets once per row;
+    // the rows of one XCD adjacent, so that its L2 holds the neighbours
     const int lane = (int)(threadIdx.x & 63);
-    const int wv = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    const int64_t nwv = (int64_t)(gridDim.x - 1) * (blockDim.x >> 6);
-    constexpr int U = 2;   // nodes per lane and round: their loads all issued before the first wait
-    constexpr int NV = 2 * DIM;
-    for (int64_t r = wv; r < rows; r += nwv) {
+    const int64_t nblk = gridDim.x - 1, per = (nblk + 7) / 8;   // (a multiple of 8 workgroups)
+    const int64_t blk = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    const int64_t wv = blk * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t nwv = nblk * (blockDim.x >> 6);
+    const int64_t each = (rows + nwv - 1) / nwv;
+    for (int64_t r = wv * each; r < min(rows, (wv + 1) * each); ++r) {
         const int iy = (int)(r % g.ny), iz = (int)(r / g.ny);
         const int64_t row = r * g.nx;
         const int64_t ym = (iy == 0) ? row + sxy - g.nx : row - g.nx;
         const int64_t yp = (iy == g.ny - 1) ? row - (sxy - g.nx) : row + g.nx;
         const int64_t zm = (iz == 0) ? row + G - sxy : row - sxy;
         const int64_t zp = (iz == g.nz - 1) ? row - (G - sxy) : row + sxy;
-        for (int ix0 = 0; ix0 < g.nx; ix0 += U * 64) {
-            // nodes past the row repeat its last node: the same values to the same addresses
-            double v[U][NV];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int ix = min(ix0 + u * 64 + lane, g.nx - 1);
-                const int xm = (ix == 0) ? g.nx - 1 : ix - 1, xp = (ix == g.nx - 1) ? 0 : ix + 1;
-                v[u][0] = phi[row + xm];
-                v[u][1] = phi[row + xp];
-                v[u][2] = phi[ym + ix];
-                v[u][3] = phi[yp + ix];
+        for (int ix0 = 0; ix0 < g.nx; ix0 += 128) {
+            if constexpr (PAIR) {
+                // two neighbouring nodes per lane (nx even), their own values the
+                // neighbour lanes' x neighbours; lanes past the row repeat its last pair
+                const int last = min(63, (g.nx - ix0) / 2 - 1), ix = ix0 + 2 * min(lane, last);
+                auto pair = [&](int64_t at) { return *(const double2 *)&phi[at + ix]; };
+                const double2 p = pair(row), y0 = pair(ym), y1 = pair(yp);
+                double2 z0 = make_double2(0.0, 0.0), z1 = z0;
                 if constexpr (DIM == 3) {
-                    v[u][4] = phi[zm + ix];
-                    v[u][5] = phi[zp + ix];
+                    z0 = pair(zm);
+                    z1 = pair(zp);
                 }
-            }
+                double edge = 0.0;
+                if (lane == 0) edge = phi[row + (ix0 == 0 ? g.nx - 1 : ix0 - 1)];
+                if (lane == last && lane > 0) edge = phi[row + (ix0 + 2 * last + 2 == g.nx ? 0 : ix0 + 2 * last + 2)];
+                double left = __shfl_up(p.y, 1), right = __shfl_down(p.x, 1);
+                if (lane == 0) left = edge;
+                if (lane >= last) right = last == 0 ? phi[row + (ix0 + 2 == g.nx ? 0 : ix0 + 2)] : edge;
+                if (lane > last) continue;
+                auto put = [&](int c, double a, double b) {
+                    const int64_t i = c * G + row + ix;
+                    if (E) *(double2 *)&E[i] = make_double2(a, b);
+                    if (E32) *(float2 *)&E32[i] = make_float2((float)a, (float)b);
+                };
+                put(0, (left - p.y) * hx, (p.x - right) * hx);
+                put(1, (y0.x - y1.x) * hy, (y0.y - y1.y) * hy);
+                if constexpr (DIM == 3) put(2, (z0.x - z1.x) * hz, (z0.y - z1.y) * hz);
+            } else {
+                constexpr int U = 2;   // nodes per lane and round: their loads all issued before the first wait
+                constexpr int NV = 2 * DIM;
+                // nodes past the row repeat its last node: the same values to the same addresses
+                double v[U][NV];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t i = row + min(ix0 + u * 64 + lane, g.nx - 1);
-                const double ex = (v[u][0] - v[u][1]) * hx, ey = (v[u][2] - v[u][3]) * hy;
-                if (E) {
-                    E[i] = ex;
-                    E[G + i] = ey;
+                for (int u = 0; u < U; ++u) {
+                    const int ix = min(ix0 + u * 64 + lane, g.nx - 1);
+                    const int xm = (ix == 0) ? g.nx - 1 : ix - 1, xp = (ix == g.nx - 1) ? 0 : ix + 1;
+                    v[u][0] = phi[row + xm];
+                    v[u][1] = phi[row + xp];
+                    v[u][2] = phi[ym + ix];
+                    v[u][3] = phi[yp + ix];
+                    if constexpr (DIM == 3) {
+                        v[u][4] = phi[zm + ix];
+                        v[u][5] = phi[zp + ix];
+                    }
                 }
-                if (E32) {
-                    E32[i] = (float)ex;
-                    E32[G + i] = (float)ey;
-                }
-                if constexpr (DIM == 3) {
-                    const double ez = (v[u][4] - v[u][5]) * hz;
-                    if (E) E[2 * G + i] = ez;
-                    if (E32) E32[2 * G + i] = (float)ez;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t i = row + min(ix0 + u * 64 + lane, g.nx - 1);
+                    const double ex = (v[u][0] - v[u][1]) * hx, ey = (v[u][2] - v[u][3]) * hy;
+                    if (E) {
+                        E[i] = ex;
+                        E[G + i] = ey;
+                    }
+                    if (E32) {
+                        E32[i] = (float)ex;
+                        E32[G + i] = (float)ey;
+                    }
+                    if constexpr (DIM == 3) {
+                        const double ez = (v[u][4] - v[u][5]) * hz;
+                        if (E) E[2 * G + i] = ez;
+                        if (E32) E32[2 * G + i] = (float)ez;
+                    }
                 }
             }
         }
@@ -1537,11 +1572,12 @@ hipError_t launch_grad(const Geo &g, const double *phi, double *E, float *E32, c
     const double hx = 0.5 * g.inv_dx, hy = 0.5 * g.inv_dy, hz = 0.5 * g.inv_dz;
     // a wave per (y, z) row, up to 8192 workgroups, then the diagnostics block
     const int64_t rows = (int64_t)g.ny * g.nz;
-    const int nblk = (int)std::min<int64_t>(std::max<int64_t>((rows + kWaves - 1) / kWaves, 1), 8192);
-    if (g.dim == 3)
-        hipLaunchKernelGGL(k_grad<3>, dim3(nblk + 1), dim3(kBlock), 0, s, g, phi, E, E32, hx, hy, hz, f, c);
-    else
-        hipLaunchKernelGGL(k_grad<2>, dim3(nblk + 1), dim3(kBlock), 0, s, g, phi, E, E32, hx, hy, hz, f, c);
+    const int nblk = (int)std::min<int64_t>((rows + 8 * kWaves - 1) / (8 * kWaves) * 8, 8192);
+    // two nodes per lane where the rows of phi and E hold whole pairs
+    const bool pair = g.nx % 2 == 0 && ((uintptr_t)E & 15) == 0 && ((uintptr_t)E32 & 7) == 0;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(nblk + 1), dim3(kBlock), 0, s, g, phi, E, E32, hx, hy, hz, f, c); };
+    if (g.dim == 3) pair ? go(k_grad<3, true>) : go(k_grad<3, false>);
+    else pair ? go(k_grad<2, true>) : go(k_grad<2, false>);
     return hipGetLastError();
 }
 
