@@ -289,8 +289,8 @@ apic_status apic_step_pair(apic_ctx *ctx, apic_particles *p, apic_particles *q, 
  * the pages of long calls, every step reorders the particles). Returns
  * APIC_EINVAL, with a message, when the workspace without those pages
  * exceeds the array, and APIC_EUNSUPPORTED for 3D
- * contexts and 2D grids whose sides are not powers of two in [4, 1024] (their
- * field solve goes through the FFT library). Every call on one GPU uses that
+ * contexts and 2D grids whose sides are not powers of two in [4, 1024].
+ * Every call on one GPU uses that
  * GPU's one array, so calls that overlap on one GPU (other streams, other
  * threads, other contexts) race; the array keeps the last call's contents,
  * and each call clears what it needs cleared. */

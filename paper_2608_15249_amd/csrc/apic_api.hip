@@ -671,7 +671,9 @@ apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ct
         delete c;
         return APIC_EHIP;
     }
-    if (d.dim == 2) {
+    // (2D grids whose solve and adjoint stay in LDS need no plans, but the start of the
+    // electromagnetic fields does, and 3D grids for the adjoint)
+    if (d.dim == 2 && (g.em || (!c->fused_fft && !c->dft_field))) {
         if (hipfftPlan2d(&c->fwd, g.ny, g.nx, HIPFFT_D2Z) != HIPFFT_SUCCESS ||
             hipfftPlan2d(&c->inv, g.ny, g.nx, HIPFFT_Z2D) != HIPFFT_SUCCESS) {
             (void)hipFree(c->dev_block);
@@ -981,8 +983,8 @@ apic_status apic_step_static(apic_ctx *c, apic_particles *p, void *rho, double *
     }
     if (c->d.dim >= 2 && !c->fused_fft)
         return fail(c, APIC_EUNSUPPORTED,
-                    "apic_step_static: the field solve of this grid uses the FFT library (3D, or 2D sides that "
-                    "are not powers of two up to 1024)");
+                    "apic_step_static: 3D grids and 2D sides that are not powers of two up to 1024 are not part of "
+                    "it");
     void *ws = nullptr;
     HIPCHK(c, scratch_address(&ws));
     return step_checked(c, p, rho, E, E32, nsteps, diag, ws, c->ws_bytes <= APIC_STATIC_WS_BYTES, (hipStream_t)stream);
