@@ -690,6 +690,7 @@ apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ct
         }
         c->have_fft = true;
     }
+    if (c->npages) (void)load_page_kernels();
     *out = c;
     return APIC_OK;
 }

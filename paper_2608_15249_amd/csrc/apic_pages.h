@@ -63,6 +63,9 @@ struct PageField {
 // beside the workgroups of a whole chip.
 inline bool page_field_folds(const Geo &g) { return g.dim == 1 && g.nx <= 2048; }
 
+// Brings the kernels of this file onto the device, which their first launch would
+// do otherwise.
+hipError_t load_page_kernels();
 hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int32_t *nfar3, int64_t n,
                              int64_t max_per_bucket, const int32_t *bstart, uint64_t *acc, int64_t nacc,
                              const CtxDev &c, hipStream_t s);

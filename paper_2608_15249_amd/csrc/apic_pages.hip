@@ -1263,6 +1263,11 @@ __global__ void __launch_bounds__(kBlock) k_page_end(Geo g, PageStep t, int64_t 
 
 // ================================================================ launchers
 
+hipError_t load_page_kernels() {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, (const void *)k_page_fill);
+}
+
 hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int32_t *nfar3, int64_t n,
                              int64_t max_per_bucket, const int32_t *bstart, uint64_t *acc, int64_t nacc,
                              const CtxDev &c, hipStream_t s) {
