@@ -225,7 +225,7 @@ def run_path(precision, w, state, steps, warmup, tile, torch, pusher="boris", c_
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None if traffic is None else traffic / (push_ms * 1e-3) / 1e9,
-                     "kernel": "k_step_push (gather+%s+move+deposit+scatter)" % ("Higuera-Cary" if pusher == "hc" else "Boris"),
+                     "kernel": "k_page_push (exchange+gather+%s+move+deposit, in place)" % ("Higuera-Cary" if pusher == "hc" else "Boris"),
                      "bytes_per_launch": push_bytes,
                      "atomics": atomics_of(counters, n, push_ms)},
         "final_WE": float(d[-1, 1]),
@@ -295,8 +295,8 @@ def run_em(precision, w, state, steps, warmup, tile, c_light, torch):
                                       "count+scan+push": n / ((ms[0] + ms[1] + ms[2]) / nprof * 1e-3)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_step_push, electromagnetic form (staggered gather+Boris+move+Esirkepov "
-                               "current+scatter)",
+                     "kernel": "k_page_push, electromagnetic form (exchange+staggered gather+Boris+move+Esirkepov "
+                               "current, in place)",
                      "bytes_per_launch": push_bytes},
         "final_W_B": float(d[-1, 0]),
         "final_W_E": float(d[-1, 1]),
