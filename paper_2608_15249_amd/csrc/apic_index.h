@@ -1,0 +1,19 @@
+// Index rules of kernels whose rounds start before a bucket's first particle
+// or end behind its last. Plain functions of the counts without any HIP type,
+// so that the CPU tests can go through them.
+#pragma once
+
+namespace apic {
+
+// Copy of a paged bucket back to the caller's arrays (k_page_end): rounds of
+// `width` places, the first from the line boundary `ahead` places before the
+// bucket's own first one. An empty bucket has no round: it has no page either.
+constexpr int copy_rounds(int count, int ahead, int width) {
+    return count > 0 ? (int)(((unsigned)count + (unsigned)ahead + (unsigned)width - 1) / (unsigned)width) : 0;
+}
+
+// The particle read for place k of such a round (count > 0): the nearest one
+// of the bucket where k lies outside it.
+constexpr int copy_slot(int k, int count) { return k < 0 ? 0 : k < count ? k : count - 1; }
+
+}  // namespace apic

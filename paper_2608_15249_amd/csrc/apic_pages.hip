@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "apic_index.h"
 #include "apic_pages.h"
 #include "apic_step.h"
 
@@ -1243,11 +1244,13 @@ __global__ void __launch_bounds__(kBlock) k_page_end(Geo g, PageStep t, int64_t 
         // first place, so that the waves store whole lines
         constexpr int P = 4;
         const int ahead = dsb & (MIX ? 31 : 15);
-        for (int k0 = -ahead; k0 < count; k0 += P * kBlock) {
+        const int rounds = copy_rounds(count, ahead, P * kBlock);
+        for (int q = 0; q < rounds; ++q) {
+            const int k0 = q * P * kBlock - ahead;
             Raw<MIX> r[P];
 #pragma unroll
             for (int j = 0; j < P; ++j) {
-                const int k = min(max(k0 + j * kBlock + (int)threadIdx.x, 0), count - 1);
+                const int k = copy_slot(k0 + j * kBlock + (int)threadIdx.x, count);
                 load_slot<MIX, DIM, VDIM>(page_at<MIX, DIM, VDIM>(t, t.tab[psb + k / kPage]), k % kPage, r[j]);
             }
 #pragma unroll

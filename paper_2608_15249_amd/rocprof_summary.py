@@ -31,7 +31,7 @@ import re
 import sqlite3
 
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
-KERNEL_SOURCES = ("apic_kernels.hip", "apic_pages.hip", "apic_pages.h", "apic_step.h", "apic_device.h", "apic_internal.h",
+KERNEL_SOURCES = ("apic_kernels.hip", "apic_pages.hip", "apic_pages.h", "apic_index.h", "apic_step.h", "apic_device.h", "apic_internal.h",
                   "apic_em.h")
 
 

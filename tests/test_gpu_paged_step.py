@@ -6,7 +6,8 @@ to rounding), FP64 path to rounding amplified over the steps. The sizes are
 those where the exchange can go wrong: partial tiles, tiles that are their own
 neighbours, jumps beyond the neighbour tiles, buckets that empty and fill
 (pages taken and given back, compaction beyond one bitmap), absorbing walls,
-a bucket without a particle, more buckets than one launch scans."""
+more buckets than one launch scans. (Buckets without a particle:
+test_gpu_paged_empty.py.)"""
 import numpy as np
 import pytest
 

@@ -1,0 +1,44 @@
+"""Index rules of kernels whose rounds run past a bucket (csrc/apic_index.h), compiled for the CPU and gone through at the
+counts where they can go wrong: every index that such a round reads lies inside the bucket, every particle is met once."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2608_15249_amd", "csrc")
+
+
+def run(tmp_path, body):
+    src = tmp_path / "rules.cpp"
+    src.write_text('#include "apic_index.h"\n#include <climits>\n#include <cstdint>\n#include <cstdio>\n#include <vector>\n'
+                   "using namespace apic;\nint main() {\n" + body + "\nreturn 0;\n}\n")
+    exe = tmp_path / "rules"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", CSRC,
+                           "-o", str(exe), str(src)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("line", [16, 32])
+def test_copy_of_a_bucket_stays_inside_it(tmp_path, line):
+    """k_page_end: empty buckets and every start inside a line."""
+    run(tmp_path, """
+    const int width = 4 * 256;
+    for (int ahead = 0; ahead < %d; ++ahead)
+        for (int count : {0, 1, 15, 16, 17, 31, 32, 33, 127, 128, 1000, 1023, 1024, 1025, 5000}) {
+            std::vector<int> met(count, 0);
+            const int rounds = copy_rounds(count, ahead, width);
+            if (count == 0 && rounds != 0) { std::printf("an empty bucket is read (ahead %%d)\\n", ahead); return 1; }
+            for (int q = 0; q < rounds; ++q)
+                for (int i = 0; i < width; ++i) {
+                    const int k = q * width - ahead + i, s = copy_slot(k, count);
+                    if (s < 0 || s >= count) { std::printf("slot %%d of %%d (ahead %%d)\\n", s, count, ahead); return 1; }
+                    if (k >= 0 && k < count) {
+                        if (s != k) return 1;
+                        ++met[k];
+                    }
+                }
+            for (int m : met) if (m != 1) { std::printf("met %%d times\\n", m); return 1; }
+        }
+    """ % line)
