@@ -196,7 +196,8 @@ void layout(apic_ctx *c) {
     c->o_phole = take(2 * 4 * n);
     c->o_pcode = take(2 * n);
     c->o_porder = take(2 * 4 * n);
-    c->o_pfar = take(2 * 2 * 4 * n);
+    c->o_pfar = take(2 * 4 * n);
+    c->o_pfarhead = take(2 * 4 * nb * kFarChains);
     c->o_plcnt = take(2 * 4 * nb * kStepTab);
     c->o_ploff = take(2 * 4 * nb * kStepTab);
     c->o_pcnt = take(3 * 4 * nb);
@@ -225,14 +226,12 @@ PageStep page_step(const apic_ctx *c, void *ws, int k) {
     t.queue = wsp<int32_t>(ws, c->o_pqueue);
     t.head = wsp<unsigned long long>(ws, c->o_phead);
     t.npages = c->npages;
-    int32_t *words = (int32_t *)(t.head + 2);   // three far counters, the live count, the buckets done
-    t.live = words + 3;
-    t.done = words + 4;
-    t.nfar_clear = words + (z + 1) % 3;
+    t.live = (int32_t *)(t.head + 2);
+    t.done = t.live + 1;
     t.pool = wsp<char>(ws, c->o_pool);
     t.out_slots = paged_slots(n);
     const size_t state = particle_bytes(c);
-    auto list = [&](int side, int nfar) {
+    auto list = [&](int side) {
         PageList l{};
         l.cnt = wsp<int32_t>(ws, c->o_plcnt) + side * nb * kStepTab;
         l.off = wsp<int32_t>(ws, c->o_ploff) + side * nb * kStepTab;
@@ -240,20 +239,19 @@ PageStep page_step(const apic_ctx *c, void *ws, int k) {
         l.raw_code = wsp<uint8_t>(ws, c->o_pcode) + side * n;
         l.hole = wsp<int32_t>(ws, c->o_phole) + side * n;
         l.order = wsp<int32_t>(ws, c->o_porder) + side * n;
-        l.far = wsp<int32_t>(ws, c->o_pfar) + side * 2 * n;
-        l.far_dest = l.far + n;
-        l.nfar = words + nfar;
+        l.far_head = wsp<int32_t>(ws, c->o_pfarhead) + side * nb * kFarChains;
+        l.far_next = wsp<int32_t>(ws, c->o_pfar) + side * n;
         l.out = wsp<char>(ws, c->o_out) + side * t.out_slots * state;
         return l;
     };
-    t.in = list(b, (z + 2) % 3);
-    t.to = list(a, z);
+    t.in = list(b);
+    t.to = list(a);
     return t;
 }
 
 apic_status page_begin(apic_ctx *c, const int32_t *bstart, void *acc, int64_t nacc, void *ws, hipStream_t s) {
     const PageStep t = page_step(c, ws, 0);
-    HIPCHK(c, launch_page_begin(c->g, t, wsp<int32_t>(ws, c->o_pcnt), (int32_t *)(t.head + 2), c->n, max_per_bucket(c),
+    HIPCHK(c, launch_page_begin(c->g, t, wsp<int32_t>(ws, c->o_pcnt), wsp<int32_t>(ws, c->o_pfarhead), c->n, max_per_bucket(c),
                                 bstart, (uint64_t *)acc, nacc, c->dev, s));
     return APIC_OK;
 }

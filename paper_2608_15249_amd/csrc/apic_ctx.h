@@ -38,7 +38,7 @@ struct apic_ctx {
     // it shares the front of the workspace with the arrays that only the sort
     // and the reordering step use
     int64_t npages = 0;
-    size_t o_pool, o_out, o_ptab, o_pqueue, o_phead, o_praw, o_phole, o_pcode, o_porder, o_pfar, o_plcnt, o_ploff,
+    size_t o_pool, o_out, o_ptab, o_pqueue, o_phead, o_praw, o_phole, o_pcode, o_porder, o_pfar, o_pfarhead, o_plcnt, o_ploff,
         o_pcnt, o_pds, o_pps;
     size_t ws_bytes;
     size_t ws_step_bytes;     // the workspace without the paged storage's part beyond the shared front

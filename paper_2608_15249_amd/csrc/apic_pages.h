@@ -13,6 +13,10 @@ namespace apic {
 // 33.5M).
 constexpr int kPage = 128;
 constexpr int kPagePushMax = 512;  // threads of a push workgroup, at most
+// Chains of a bucket's far arrivals, one per lane of the wave that walks them: a
+// bucket reads its own arrivals alone, and the chain a leaver joins (its lane's)
+// keeps the heads' atomics apart.
+constexpr int kFarChains = 64;
 
 // The leavers of one step, bucket by bucket (a bucket's entries start at its ds).
 struct PageList {
@@ -20,8 +24,11 @@ struct PageList {
     int32_t *raw_slot;        // [n] their slots, as listed (their state: the same entries of out)
     uint8_t *raw_code;        // [n] their directions, as listed
     int32_t *hole, *order;    // [n] their slots and outbox entries in direction order
-    int32_t *far, *far_dest;  // [n] outbox entries of those bound beyond the neighbours, their buckets
-    int32_t *nfar;            // [1] their number
+    // those bound beyond the neighbours, chained by destination: chain c of bucket
+    // b starts at far_head[b * kFarChains + c] and goes on at far_next[entry]; both
+    // hold an outbox entry + 1, 0 at the end
+    int32_t *far_head;        // [nb][kFarChains], zero once read
+    int32_t *far_next;        // [n], by outbox entry
     char *out;                // [out_slots] outbox, in pieces as the pages
 };
 
@@ -44,7 +51,6 @@ struct PageStep {
     int64_t npages;
     int32_t *live;                   // [1] particles not absorbed by a wall
     int32_t *done;                   // [1] buckets whose 1D push has ended, zero between the steps
-    int32_t *nfar_clear;             // [1] the next step's PageList::nfar
     char *pool;                      // [npages] pages
     int64_t out_slots;               // n rounded up
     PageList in, to;                 // leavers of the step before, of this one
@@ -66,7 +72,8 @@ inline bool page_field_folds(const Geo &g) { return g.dim == 1 && g.nx <= 2048; 
 // Brings the kernels of this file onto the device, which their first launch would
 // do otherwise.
 hipError_t load_page_kernels();
-hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int32_t *nfar3, int64_t n,
+// t: the call's first step, head2 [2][nb][kFarChains]: the chain heads of both sides
+hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int32_t *head2, int64_t n,
                              int64_t max_per_bucket, const int32_t *bstart, uint64_t *acc, int64_t nacc,
                              const CtxDev &c, hipStream_t s);
 // src: the caller's arrays (with bstart) in a call's first step, else NULL
