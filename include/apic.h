@@ -561,6 +561,9 @@ const char *apic_batch_last_error(const apic_batch *b);
  * (the caller's arrays are only read), returns the fastest candidate and
  * its ms per step, and caches the pick for the process: a later call for the
  * same shape returns the cached pick with *ms_per_step = -1 (may be NULL).
+ * nsteps should be near the length of the calls to come: apic_step keeps the
+ * particles in pages from 8 steps on, and the tiles that are best for such
+ * calls and for shorter ones differ (up to 1.8 times in time per step).
  * Returns APIC_EINVAL for bad arguments, APIC_EHIP if no candidate ran.
  *
  * apic_autotune_tiles: sort-bucket tile (tile_x, tile_y, and tile_z in 3D) for
@@ -571,7 +574,8 @@ const char *apic_batch_last_error(const apic_batch *b);
  *   apic_sort_by_cell (n > 0); bucket_start and perm are ignored. Periodic
  *   electrostatic plasmas (walls and the electromagnetic model return
  *   APIC_EUNSUPPORTED). Cache key: dim, vdim, nx, ny, nz, precision,
- *   floor(log2(particles per cell)) and the velocity advance.
+ *   floor(log2(particles per cell)), the velocity advance and whether nsteps
+ *   is 8 or more.
  * apic_batch_autotune_chunk: work-item size (particles per item, 1024 ..
  *   65535) for apic_batch_create. st: the packed initial state (cell, ox, vx;
  *   E is ignored). Cache key: total particles and replica count. */

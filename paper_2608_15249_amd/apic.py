@@ -277,9 +277,10 @@ class Context:
         self._check(self.L.apic_gather_push(self.h, ctypes.byref(s), ctypes.c_void_p(E.data_ptr()),
                                             float(dt_scale), 1 if move else 0, _stream()))
 
-    def autotune_tiles(self, parts: "Particles", nsteps: int = 5):
+    def autotune_tiles(self, parts: "Particles", nsteps: int = 20):
         """Fastest sort-bucket tile for this plasma, timed on a copy of
-        `parts` (apic_autotune_tiles). Returns (tile, ms_per_step) with tile
+        `parts` in calls of `nsteps` steps (apic_autotune_tiles): near the
+        length of the calls to come, whose path it decides. Returns (tile, ms_per_step) with tile
         (tile_x, tile_y) below 3D and (tile_x, tile_y, tile_z) in 3D;
         ms_per_step is -1 when the pick came from the process cache."""
         s = parts.struct()

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "apic.h"
+#include "apic_index.h"
 #include "apic_internal.h"
 #include "apic_pages.h"
 
@@ -92,10 +93,6 @@ int64_t max_per_bucket(const apic_ctx *c);
 apic_status field_from_acc(apic_ctx *c, void *acc, bool acc_is_rho, double *E, float *E32, double *diag,
                            double *we, double *charge, int npush, int clear, void *ws, hipStream_t s,
                            const int32_t *nlive = nullptr);
-// Calls of at least this many steps keep the particles in pages between the
-// steps: what a step saves then pays for the copy at the call's end.
-constexpr int kPagedSteps = 8;
-
 // Paged storage of a call's step k in the workspace ws, and the launches that start a call: acc (nacc 64-bit words) is
 // what the first push adds to.
 apic::PageStep page_step(const apic_ctx *c, void *ws, int k);

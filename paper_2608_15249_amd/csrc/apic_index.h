@@ -1,9 +1,14 @@
-// Index rules of kernels whose rounds start before a bucket's first particle
-// or end behind its last. Plain functions of the counts without any HIP type,
-// so that the CPU tests can go through them.
+// Rules that are plain functions of counts, without any HIP type, so that the
+// CPU tests can go through them: which calls keep the particles in pages, and
+// the indices of kernels whose rounds start before a bucket's first particle or
+// end behind its last.
 #pragma once
 
 namespace apic {
+
+// Calls of at least this many steps keep the particles in pages between the
+// steps: what a step saves then pays for the copy at the call's end.
+constexpr int kPagedSteps = 8;
 
 // Copy of a paged bucket back to the caller's arrays (k_page_end): rounds of
 // `width` places, the first from the line boundary `ahead` places before the

@@ -8,6 +8,7 @@
 // process-wide cache keyed by the problem's shape, so a later call with the
 // same shape returns at once.
 #include "apic.h"
+#include "apic_index.h"
 
 #include <hip/hip_runtime.h>
 
@@ -21,8 +22,9 @@
 
 namespace {
 
-// dim, vdim, nx, ny, nz, precision, floor(log2(particles per cell)), velocity advance
-using TileKey = std::tuple<int, int, int, int, int, int, int, int>;
+// dim, vdim, nx, ny, nz, precision, floor(log2(particles per cell)), velocity advance,
+// whether calls of the timed length may use pages
+using TileKey = std::tuple<int, int, int, int, int, int, int, int, bool>;
 using Tile = std::tuple<int, int, int>;
 
 std::mutex g_mu;
@@ -77,7 +79,12 @@ hipError_t copy_in(void *dst, const void *src, size_t bytes, hipStream_t s) {
 // four untimed steps (the first steps after the sort read every particle in
 // the tally pass and start from the sort's order), then two timed runs of
 // nsteps steps (rounded up to even, so that no run ends with the copy back
-// of an odd count), the faster of the two. Returns ms per step or INFINITY.
+// of an odd count), the faster of the two. The length of the timed calls is the
+// caller's, because it decides the path: one that reorders every step wants other
+// tiles than one that keeps the particles in pages (512 x 512, 16.8M particles, us
+// per step of calls of 6 and of 20 steps: mixed at 16 x 16 227 and 198, at 32 x 32
+// 331 and 187; FP64 at 32 x 16 302 and 289, at 32 x 32 341 and 266). Returns ms per
+// step or INFINITY.
 double trial_tiles(const apic_grid_desc &d, const apic_particles &src, const Tile &t, int nsteps, hipStream_t s) {
     apic_grid_desc dd = d;
     dd.tile_x = std::get<0>(t);
@@ -193,7 +200,7 @@ apic_status apic_autotune_tiles(const apic_grid_desc *desc, const apic_particles
         return APIC_EINVAL;
     const int ny = d.dim >= 2 ? d.ny : 1, nz = d.dim == 3 ? d.nz : 1;
     const TileKey key{d.dim, d.vdim, d.nx, ny, nz, (int)d.prec,
-                      floor_log2((double)p->n / ((double)d.nx * ny * nz)), d.pusher};
+                      floor_log2((double)p->n / ((double)d.nx * ny * nz)), d.pusher, nsteps >= apic::kPagedSteps};
     auto put = [&](const Tile &t) {
         *tile_x = std::get<0>(t);
         *tile_y = std::get<1>(t);
