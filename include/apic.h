@@ -163,6 +163,17 @@ void apic_destroy(apic_ctx *ctx);
  * only in that the library does not rely on its contents across calls. */
 apic_status apic_workspace_size(const apic_ctx *ctx, size_t *bytes);
 
+/* Bounds the workspace of the calls to come (a host call between them).
+ * Contexts with 512 particles or more per bucket on average keep room for the
+ * pages of long calls (see apic_step): four times the particles' state and 29
+ * bytes per particle, where sorting and reordering take once the state and
+ * about 5 bytes (the grids aside; magnetized 2D3V, 1024 x 1024 cells, 33.5M
+ * mixed particles of 24 bytes: 4.27 GB and 0.99 GB). Where that is more than
+ * max_bytes, every step reorders the particles and apic_workspace_size reports
+ * the bytes without pages (0: never pages; (size_t)-1: pages again). The size
+ * without pages is not bounded: compare apic_workspace_size afterwards. */
+apic_status apic_workspace_limit(apic_ctx *ctx, size_t max_bytes);
+
 /* Number of sort buckets (tiles) of the context's grid. */
 int64_t apic_num_buckets(const apic_ctx *ctx);
 

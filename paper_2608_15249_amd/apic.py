@@ -59,7 +59,7 @@ class BatchStateC(ctypes.Structure):
     _fields_ = [("cell", ctypes.c_void_p), ("ox", ctypes.c_void_p), ("vx", ctypes.c_void_p), ("E", ctypes.c_void_p)]
 
 
-EXPORTS = ["apic_create", "apic_destroy", "apic_workspace_size", "apic_num_buckets", "apic_frac_bits", "apic_tile_size",
+EXPORTS = ["apic_create", "apic_destroy", "apic_workspace_size", "apic_workspace_limit", "apic_num_buckets", "apic_frac_bits", "apic_tile_size",
            "apic_sort_by_cell", "apic_deposit", "apic_field_solve", "apic_gather_push", "apic_step",
            "apic_sync_status", "apic_last_error", "apic_profile_enable", "apic_profile_read", "apic_profile_phases",
            "apic_profile_every",
@@ -87,6 +87,7 @@ def load_library(path: str = LIB_PATH):
         "apic_create": ([P(GridDesc), i64, P(vp)], cint),
         "apic_destroy": ([vp], None),
         "apic_workspace_size": ([vp, P(ctypes.c_size_t)], cint),
+        "apic_workspace_limit": ([vp, ctypes.c_size_t], cint),
         "apic_num_buckets": ([vp], i64),
         "apic_frac_bits": ([vp], cint),
         "apic_q_macro": ([vp], dbl),
@@ -163,11 +164,13 @@ def _stream():
 
 
 class Context:
-    """One plasma on the GPU: owns the libapic context and its workspace."""
+    """One plasma on the GPU: owns the libapic context and its workspace
+    (bounded by max_workspace bytes, apic_workspace_limit, where that is given;
+    without the pages of long calls where the memory for them is not there)."""
 
     def __init__(self, *, dim, vdim, nx, ny, lx, ly, dt, n, qm=-1.0, q_macro=None, rho_ion=1.0, bz=0.0,
                  precision="mixed", frac_bits=0, tile=(0, 0), device="cuda", nz=1, lz=1.0, pusher="boris",
-                 c_light=0.0, model="es", walls=False):
+                 c_light=0.0, model="es", walls=False, max_workspace: Optional[int] = None):
         import torch
         if not torch.cuda.is_available():
             raise RuntimeError("libapic needs a HIP GPU; none is visible")
@@ -192,9 +195,13 @@ class Context:
         if st != 0:
             raise ApicError(st, "apic_create rejected the descriptor")
         self.h = h
-        sz = ctypes.c_size_t()
-        self._check(self.L.apic_workspace_size(self.h, ctypes.byref(sz)))
-        self.ws = torch.empty(max(int(sz.value), 256), dtype=torch.uint8, device=self.device)
+        if max_workspace is not None:
+            self._check(self.L.apic_workspace_limit(self.h, int(max_workspace)))
+        try:
+            self.ws = self._workspace()
+        except torch.cuda.OutOfMemoryError:
+            self._check(self.L.apic_workspace_limit(self.h, 0))
+            self.ws = self._workspace()
         self.nbuckets = int(self.L.apic_num_buckets(self.h))
         self.frac_bits = int(self.L.apic_frac_bits(self.h))
         self.q_macro = float(self.L.apic_q_macro(self.h))
@@ -205,6 +212,11 @@ class Context:
         # grid arrays of a walls context are the odd extension along x (2 nx nodes per row)
         self.nx_grid = 2 * nx if self.walls else nx
         self.G = self.nx_grid * self.ny * self.nz
+
+    def _workspace(self):
+        sz = ctypes.c_size_t()
+        self._check(self.L.apic_workspace_size(self.h, ctypes.byref(sz)))
+        return self.torch.empty(max(int(sz.value), 256), dtype=self.torch.uint8, device=self.device)
 
     def __del__(self):
         try:

@@ -192,9 +192,9 @@ void layout(apic_ctx *c) {
     c->o_ptab = take(2 * 4 * c->npages);
     c->o_pqueue = take(4 * c->npages);
     c->o_phead = take(64);
-    c->o_praw = take(2 * 4 * n);
+    c->o_praw = take(4 * n);
     c->o_phole = take(2 * 4 * n);
-    c->o_pcode = take(2 * n);
+    c->o_pcode = take(n);
     c->o_porder = take(2 * 4 * n);
     c->o_pfar = take(2 * 4 * n);
     c->o_pfarhead = take(2 * 4 * nb * kFarChains);
@@ -230,13 +230,13 @@ PageStep page_step(const apic_ctx *c, void *ws, int k) {
     t.done = t.live + 1;
     t.pool = wsp<char>(ws, c->o_pool);
     t.out_slots = paged_slots(n);
+    t.raw_slot = wsp<int32_t>(ws, c->o_praw);
+    t.raw_code = wsp<uint8_t>(ws, c->o_pcode);
     const size_t state = particle_bytes(c);
     auto list = [&](int side) {
         PageList l{};
         l.cnt = wsp<int32_t>(ws, c->o_plcnt) + side * nb * kStepTab;
         l.off = wsp<int32_t>(ws, c->o_ploff) + side * nb * kStepTab;
-        l.raw_slot = wsp<int32_t>(ws, c->o_praw) + side * n;
-        l.raw_code = wsp<uint8_t>(ws, c->o_pcode) + side * n;
         l.hole = wsp<int32_t>(ws, c->o_phole) + side * n;
         l.order = wsp<int32_t>(ws, c->o_porder) + side * n;
         l.far_head = wsp<int32_t>(ws, c->o_pfarhead) + side * nb * kFarChains;
@@ -707,6 +707,16 @@ void apic_destroy(apic_ctx *c) {
 apic_status apic_workspace_size(const apic_ctx *c, size_t *bytes) {
     if (!c || !bytes) return APIC_EINVAL;
     *bytes = c->ws_bytes;
+    return APIC_OK;
+}
+
+apic_status apic_workspace_limit(apic_ctx *c, size_t max_bytes) {
+    if (!c) return APIC_EINVAL;
+    layout(c);
+    if (c->ws_bytes > max_bytes) {
+        c->npages = 0;
+        c->ws_bytes = c->ws_step_bytes;
+    }
     return APIC_OK;
 }
 

@@ -21,8 +21,6 @@ constexpr int kFarChains = 64;
 // The leavers of one step, bucket by bucket (a bucket's entries start at its ds).
 struct PageList {
     int32_t *cnt, *off;       // [nb][directions] leavers, the first one's place in the bucket's list
-    int32_t *raw_slot;        // [n] their slots, as listed (their state: the same entries of out)
-    uint8_t *raw_code;        // [n] their directions, as listed
     int32_t *hole, *order;    // [n] their slots and outbox entries in direction order
     // those bound beyond the neighbours, chained by destination: chain c of bucket
     // b starts at far_head[b * kFarChains + c] and goes on at far_next[entry]; both
@@ -53,6 +51,10 @@ struct PageStep {
     int32_t *done;                   // [1] buckets whose 1D push has ended, zero between the steps
     char *pool;                      // [npages] pages
     int64_t out_slots;               // n rounded up
+    // this launch's own scratch, a bucket's part where its entries of ds start
+    int32_t *raw_slot;               // [n] the leavers' slots, as listed (their state: the same entries of
+                                     // to.out); during the exchange the holes that a shrinking bucket keeps
+    uint8_t *raw_code;               // [n] their directions, as listed
     PageList in, to;                 // leavers of the step before, of this one
 };
 

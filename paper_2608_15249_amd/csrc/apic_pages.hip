@@ -564,9 +564,10 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
         if (np_new > np_old) sh.q = atomicAdd(&t.head[0], (unsigned long long)(np_new - np_old));
         if (np_new < np_old) sh.q = atomicAdd(&t.head[1], (unsigned long long)(np_old - np_new));
     }
-    int pn;
+    int pn, dn;   // the bucket's first entries now
     if constexpr (SCANNED) {
         pn = t.ps[b];
+        dn = t.ds[b];
         __syncthreads();
     } else {
         int64_t d = 0;
@@ -591,8 +592,9 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
             d += sh.d[i];
             pn += sh.p[i];
         }
+        dn = (int)d;
         if (threadIdx.x == 0) {
-            t.ds[b] = (int32_t)d;
+            t.ds[b] = dn;
             t.ps[b] = pn;
             if (now > max_per) raise_err(c.err, ERR_OVERFLOW);
             if (b == nb - 1) {
@@ -620,7 +622,7 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
     if (now < old) {
         // a shrinking bucket: the holes below its new end, then the particles
         // beyond it into those that no arrival takes
-        int32_t *keep = t.in.raw_slot + dsb;
+        int32_t *keep = t.raw_slot + dn;   // (fewer than the bucket will hold)
         int nlow = 0;
         for (int e0 = 0; e0 < nout; e0 += blockDim.x) {
             const int e = e0 + (int)threadIdx.x;
@@ -950,8 +952,8 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                 if (m) {
                     if (leaves) {
                         const int at = seg + nlist + (int)__popcll(m & lt);
-                        t.to.raw_slot[at] = k;
-                        t.to.raw_code[at] = (uint8_t)code;
+                        t.raw_slot[at] = k;
+                        t.raw_code[at] = (uint8_t)code;
                         out_put<MIX, DIM, VDIM>(t, at, r[j]);
                         atomicAdd(&sCnt[code], 1);
                         if (code == kFar) far_leaver(at, nbk);
@@ -1108,8 +1110,8 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                                     deposit_global<MIX, DIM>(acc, g, q.ix, q.iy, wgt);
                             }
                             const int at = seg + nlist + (int)__popcll(mk & lt);
-                            t.to.raw_slot[at] = (w + i * nw) * kPage + (h + j) * 64 + lane;
-                            t.to.raw_code[at] = (uint8_t)code;
+                            t.raw_slot[at] = (w + i * nw) * kPage + (h + j) * 64 + lane;
+                            t.raw_code[at] = (uint8_t)code;
                             out_put<MIX, DIM, VDIM>(t, at, r[h + j]);
                             atomicAdd(&sCnt[code], 1);
                             if (code == kFar) far_leaver(at, bucket_of<MIX, DIM>(g, q.ix, q.iy, q.iz));
@@ -1194,8 +1196,8 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
                     r -= sList[w2];
                     before += units;
                 }
-                slot = t.to.raw_slot[at];
-                code = t.to.raw_code[at];
+                slot = t.raw_slot[at];
+                code = t.raw_code[at];
             }
             uint64_t peers = __ballot(code >= 0);
 #pragma unroll

@@ -34,8 +34,10 @@ std::map<std::pair<int64_t, int>, int> g_chunks;  // (total particles, replicas)
 struct DevBuf {
     void *p = nullptr;
     bool ok = true;
-    explicit DevBuf(size_t n) {
-        if (n) ok = hipMalloc(&p, n) == hipSuccess;
+    explicit DevBuf(size_t n) { get(n); }
+    void get(size_t n) {
+        ok = !n || hipMalloc(&p, n) == hipSuccess;
+        if (!ok) (void)hipGetLastError();   // (not for the next launch to report)
     }
     ~DevBuf() {
         if (p) (void)hipFree(p);
@@ -95,11 +97,18 @@ double trial_tiles(const apic_grid_desc &d, const apic_particles &src, const Til
     const bool mixed = d.prec == APIC_MIXED;
     const size_t n = (size_t)src.n, r = mixed ? 4 : 8;
     const size_t G = (size_t)d.nx * (d.dim >= 2 ? d.ny : 1) * (d.dim == 3 ? d.nz : 1);
-    size_t wsb = 0;
-    (void)apic_workspace_size(c, &wsb);
-    DevBuf ws(wsb), pa(r * n), pb(d.dim >= 2 ? r * n : 0), pc(d.dim == 3 ? r * n : 0), cell(mixed ? 4 * n : 0),
+    DevBuf pa(r * n), pb(d.dim >= 2 ? r * n : 0), pc(d.dim == 3 ? r * n : 0), cell(mixed ? 4 * n : 0),
         vx(r * n), vy(d.vdim >= 2 ? r * n : 0), vz(d.vdim >= 3 ? r * n : 0),
         bs(4 * ((size_t)apic_num_buckets(c) + 1)), rho(8 * G), E(8 * G * d.dim);
+    // where the memory for pages is not there, the candidate is timed without them
+    size_t wsb = 0;
+    (void)apic_workspace_size(c, &wsb);
+    DevBuf ws(wsb);
+    if (!ws.ok) {
+        (void)apic_workspace_limit(c, 0);
+        (void)apic_workspace_size(c, &wsb);
+        ws.get(wsb);
+    }
     double out = INFINITY;
     if (ws.ok && pa.ok && pb.ok && pc.ok && cell.ok && vx.ok && vy.ok && vz.ok && bs.ok && rho.ok && E.ok) {
         apic_particles p{};

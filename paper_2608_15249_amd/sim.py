@@ -26,16 +26,17 @@ class Simulation:
         if state is None:
             state = W.sample3(w, n) if w.dim == 3 else W.sample(w, n)
         self.n = len(state[0])
-        mk = lambda t: Context(dim=w.dim, vdim=w.vdim, nx=w.nx, ny=w.ny, lx=w.Lx, ly=w.Ly, dt=w.dt, n=self.n,
+        mk = lambda t, **kw: Context(dim=w.dim, vdim=w.vdim, nx=w.nx, ny=w.ny, lx=w.Lx, ly=w.Ly, dt=w.dt, n=self.n,
                                bz=w.bz, precision=precision, frac_bits=frac_bits, tile=t, device=device,
-                               nz=w.nz, lz=w.Lz, pusher=pusher, c_light=c_light, walls=walls)
+                               nz=w.nz, lz=w.Lz, pusher=pusher, c_light=c_light, walls=walls, **kw)
         self.tune_ms = None
         if tile == "auto" and walls:
             # the tile autotuner covers periodic plasmas; between walls the default tile is kept
             tile = (0, 0)
         if tile == "auto":
             # time the candidate tiles on this very state, then build the context with the pick
-            ctx = mk((0, 0, 0) if w.dim == 3 else (0, 0))
+            # (the context that holds the state meanwhile makes no steps: the least workspace)
+            ctx = mk((0, 0, 0) if w.dim == 3 else (0, 0), max_workspace=0)
             p = Particles(ctx)
             self._upload(p, ctx.mixed, state)
             tile, self.tune_ms = ctx.autotune_tiles(p)
