@@ -21,4 +21,11 @@ constexpr int copy_rounds(int count, int ahead, int width) {
 // of the bucket where k lies outside it.
 constexpr int copy_slot(int k, int count) { return k < 0 ? 0 : k < count ? k : count - 1; }
 
+
+// The particle loaded for place k of the bucket of `count` particles from
+// `first` on (tiled deposit and gather + push, several places ahead of their
+// use). k is unsigned and counts from the bucket's start: there are up to
+// 2^31 - 2 particles, and the places run past a bucket by a round.
+constexpr int ahead_index(int first, unsigned k, unsigned count) { return first + (int)(k < count ? k : count - 1); }
+
 }  // namespace apic

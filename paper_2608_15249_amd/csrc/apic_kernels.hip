@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "apic_index.h"
 #include "apic_step.h"
 
 namespace apic {
@@ -173,13 +174,14 @@ __global__ void __launch_bounds__(kBlock) k_deposit_tiled(Geo g, Parts p, const 
     for (int t = threadIdx.x; t < wx * wy * wz; t += blockDim.x) sA[t] = (A)0;
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    for (int base = i0 + threadIdx.x; base < i1; base += kAhead * blockDim.x) {
+    const unsigned count = i1 - i0, ahead = kAhead * blockDim.x;
+    for (unsigned k0 = threadIdx.x; k0 < count; k0 += ahead) {
         Raw<MIX> r[kAhead];
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, 0>(p, min(base + j * (int)blockDim.x, i1 - 1), r[j]);
+        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, 0>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
-            if (base + j * (int)blockDim.x >= i1) break;
+            if (k0 + j * blockDim.x >= count) break;
             Pt<MIX> q;
             if (!decode<MIX, DIM, 0>(r[j], g, q)) {
                 raise_err(c.err, ERR_DOMAIN);
@@ -269,14 +271,15 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, co
         load_e_tile<R, R, DIM>(sE, E, g, x0, y0, ex_w, ey_w);
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    for (int base = i0 + threadIdx.x; base < i1; base += kAhead * blockDim.x) {
+    const unsigned count = i1 - i0, ahead = kAhead * blockDim.x;
+    for (unsigned k0 = threadIdx.x; k0 < count; k0 += ahead) {
         Raw<MIX> r[kAhead];
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, VDIM>(p, min(base + j * (int)blockDim.x, i1 - 1), r[j]);
+        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, VDIM>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
-            const int i = base + j * (int)blockDim.x;
-            if (i >= i1) break;
+            if (k0 + j * blockDim.x >= count) break;
+            const int i = i0 + (int)(k0 + j * blockDim.x);
             Pt<MIX> q;
             if (!decode<MIX, DIM, VDIM>(r[j], g, q)) {
                 raise_err(c.err, ERR_DOMAIN);

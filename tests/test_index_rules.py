@@ -42,3 +42,28 @@ def test_copy_of_a_bucket_stays_inside_it(tmp_path, line):
             for (int m : met) if (m != 1) { std::printf("met %%d times\\n", m); return 1; }
         }
     """ % line)
+
+
+def test_places_ahead_at_the_largest_bucket(tmp_path):
+    """Tiled deposit and gather + push: the last rounds of buckets up to the largest particle count, wherever they lie in
+    the arrays (places counted in a signed word from the arrays' start wrap there)."""
+    run(tmp_path, """
+    const unsigned block = 256, per = 4;
+    const int most = INT_MAX - 1;
+    for (int count : {1, 255, 256, 1023, 1024, 1025, most - 1025, most - 1, most})
+        for (int64_t first : {(int64_t)0, (int64_t)(most - count) / 2, (int64_t)most - count})
+            for (unsigned thread : {0u, 1u, 255u}) {
+                // from a round near the bucket's end on
+                const unsigned c = (unsigned)count, ahead = per * block;
+                const unsigned from = thread + (c > 3 * ahead ? (c / ahead - 2) * ahead : 0);
+                int64_t met = 0;
+                for (unsigned k0 = from; k0 < c; k0 += ahead) {
+                    if (++met > 8) return 1;   // wrapped
+                    for (unsigned j = 0; j < per; ++j) {
+                        const int64_t i = ahead_index((int)first, k0 + j * block, c);
+                        if (i < first || i >= first + count) { std::printf("%lld\\n", (long long)i); return 1; }
+                        if (k0 + j * block < c && i != first + (int64_t)(k0 + j * block)) return 1;
+                    }
+                }
+            }
+    """)
