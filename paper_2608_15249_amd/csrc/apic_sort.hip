@@ -2,12 +2,12 @@
 // that move the particles themselves.
 //
 // A pass orders by the next digit of the bucket index. Every workgroup takes a
-// chunk of kChunk particles, ranks them by digit (wave by wave, so equal digits
-// keep their order), and writes the chunk through LDS in digit order: each
-// digit's particles of a chunk form one run of consecutive places, so that every
+// chunk of 512 to 4096 particles (per_of below), ranks them by digit (wave by
+// wave, so equal digits keep their order), and writes the chunk through LDS in
+// digit order: each digit's particles of a chunk form one run of consecutive places, so that every
 // array is read and written in whole lines. Digits are as short as the passes
 // allow (two passes of half the bits up to 65536 buckets, else four): shorter
-// digits are longer runs (1024 buckets: 32 digits, 128 particles a run). The
+// digits are longer runs (1024 buckets: 32 digits, 64 particles a run of 2048). The
 // number of passes is even, so the state returns to the caller's arrays without
 // a copy; the input index travels as one more array where the caller wants the
 // permutation.
@@ -24,8 +24,6 @@
 namespace apic {
 namespace {
 
-constexpr int kPer = 16;                 // particles per thread and chunk
-constexpr int kChunk = kBlock * kPer;    // particles per chunk
 constexpr int kScan = 2048;              // tallies per workgroup of the scan
 constexpr int kMaxDigits = 256;
 
@@ -62,16 +60,17 @@ __device__ __forceinline__ int key_of(const Geo &g, const Parts &p, int64_t i, b
 
 // Digit tallies of every chunk, digit-major: cnt[d * chunks + chunk]. CHECK (the
 // first pass): invalid particles are reported.
-template <bool MIX, int DIM, int VDIM, bool CHECK>
+// PER particles per thread: a chunk is kBlock * PER.
+template <bool MIX, int DIM, int VDIM, int PER, bool CHECK>
 __global__ void __launch_bounds__(kBlock) k_sort_count(Geo g, Parts p, int64_t n, int shift, int bits, int32_t *cnt,
                                                        CtxDev c) {
     __shared__ int32_t s[kMaxDigits];
     const int nd = 1 << bits;
     for (int d = threadIdx.x; d < nd; d += kBlock) s[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kChunk + threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (kBlock * PER) + threadIdx.x;
     bool good = true;
-    for (int j = 0; j < kPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const int64_t i = base + j * kBlock;
         if (i < n) {
             bool ok;
@@ -106,7 +105,7 @@ __device__ __forceinline__ int block_prefix(int v, int &total, int32_t *sh /* [k
 }
 
 // The tallies become exclusive sums inside each group of kScan, and the groups'
-// totals go to part.
+// totals go to part (a single group: zero, the sum of those before it).
 __global__ void __launch_bounds__(kBlock) k_sort_scan(int32_t *cnt, int64_t m, int32_t *part) {
     __shared__ int32_t sh[kWaves];
     constexpr int P = kScan / kBlock;
@@ -124,7 +123,7 @@ __global__ void __launch_bounds__(kBlock) k_sort_scan(int32_t *cnt, int64_t m, i
         if (base + j < m) cnt[base + j] = run;
         run += v[j];
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = total;
+    if (threadIdx.x == 0) part[blockIdx.x] = gridDim.x == 1 ? 0 : total;
 }
 
 // Exclusive sums of the groups' totals (one workgroup).
@@ -144,30 +143,30 @@ __global__ void __launch_bounds__(kBlock) k_sort_base(int32_t *part, int groups)
 // One array of the chunk to its places: through LDS into digit order, then in
 // runs. pos: this thread's places inside the chunk, dst: the global place of
 // chunk position j * kBlock + thread.
-template <typename T>
+template <int PER, typename T>
 __device__ __forceinline__ void move_array(const T *in, T *out, T *s, int64_t i0, int64_t n, int m, const int *pos,
                                            const int32_t *dst) {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    T v[kPer];
+    T v[PER];
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int k = w * 64 * kPer + j * 64 + lane;
+    for (int j = 0; j < PER; ++j) {
+        const int k = w * 64 * PER + j * 64 + lane;
         v[j] = in[min(i0 + k, n - 1)];
     }
     __syncthreads();   // the previous array has left LDS
 #pragma unroll
-    for (int j = 0; j < kPer; ++j)
+    for (int j = 0; j < PER; ++j)
         if (pos[j] >= 0) s[pos[j]] = v[j];
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const int k = j * kBlock + threadIdx.x;
         if (k < m) out[dst[j]] = s[k];
     }
 }
 
 // idx_in NULL with idx_out set: the input index starts here.
-template <bool MIX, int DIM, int VDIM>
+template <bool MIX, int DIM, int VDIM, int PER>
 __global__ void __launch_bounds__(kBlock) k_sort_move(Geo g, Parts in, Parts out, int64_t n, int shift, int bits,
                                                       const int32_t *cnt, const int32_t *part, const int32_t *idx_in,
                                                       int32_t *idx_out, CtxDev c) {
@@ -175,19 +174,19 @@ __global__ void __launch_bounds__(kBlock) k_sort_move(Geo g, Parts in, Parts out
     extern __shared__ __align__(16) unsigned char smem[];   // one array of the chunk
     __shared__ int32_t sRun[kWaves][kMaxDigits];            // next place of each (wave, digit)
     __shared__ int32_t sGlob[kMaxDigits];                   // global place of a digit's run less its place in the chunk
-    __shared__ uint8_t sDig[kChunk];                        // digit of each chunk position
+    __shared__ uint8_t sDig[kBlock * PER];                  // digit of each chunk position
     __shared__ int32_t sh[kWaves];
     const int nd = 1 << bits, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t i0 = (int64_t)blockIdx.x * kChunk;
-    const int m = (int)min((int64_t)kChunk, n - i0);
+    const int64_t i0 = (int64_t)blockIdx.x * (kBlock * PER);
+    const int m = (int)min((int64_t)(kBlock * PER), n - i0);
     for (int d = threadIdx.x; d < kWaves * kMaxDigits; d += kBlock) (&sRun[0][0])[d] = 0;
     __syncthreads();
-    // wave w owns the consecutive particles [w, w + 1) * 64 * kPer of the chunk; ranks inside (wave, digit)
+    // wave w owns the consecutive particles [w, w + 1) * 64 * PER of the chunk; ranks inside (wave, digit)
     const uint64_t lt = lanemask_lt();
-    int pos[kPer], dig[kPer];
+    int pos[PER], dig[PER];
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int k = w * 64 * kPer + j * 64 + lane;
+    for (int j = 0; j < PER; ++j) {
+        const int k = w * 64 * PER + j * 64 + lane;
         const bool act = k < m;
         bool ok;
         const int key = key_of<MIX, DIM, VDIM>(g, in, min(i0 + k, n - 1), ok);
@@ -231,24 +230,26 @@ __global__ void __launch_bounds__(kBlock) k_sort_move(Geo g, Parts in, Parts out
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         if (pos[j] >= 0) {
             pos[j] += sRun[w][dig[j]];
             sDig[pos[j]] = (uint8_t)dig[j];
         }
     }
     __syncthreads();
-    int32_t dst[kPer];
+    int32_t dst[PER];
     bool bad = false;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const int k = j * kBlock + (int)threadIdx.x;
         const int64_t to = k < m ? (int64_t)sGlob[sDig[k]] + k : 0;
         bad = bad || to < 0 || to >= n;
         dst[j] = (int32_t)min(max(to, (int64_t)0), n - 1);
     }
     if (bad) raise_err(c.err, ERR_ORDER);
-    auto mv = [&](auto *a, auto *b) { move_array(a, b, (std::remove_reference_t<decltype(*b)> *)smem, i0, n, m, pos, dst); };
+    auto mv = [&](auto *a, auto *b) {
+        move_array<PER>(a, b, (std::remove_reference_t<decltype(*b)> *)smem, i0, n, m, pos, dst);
+    };
     if constexpr (MIX) {
         mv(in.cell, out.cell);
         mv(in.ox, out.ox);
@@ -269,11 +270,11 @@ __global__ void __launch_bounds__(kBlock) k_sort_move(Geo g, Parts in, Parts out
             int32_t *s = (int32_t *)smem;
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < kPer; ++j)
-                if (pos[j] >= 0) s[pos[j]] = (int32_t)(i0 + w * 64 * kPer + j * 64 + lane);
+            for (int j = 0; j < PER; ++j)
+                if (pos[j] >= 0) s[pos[j]] = (int32_t)(i0 + w * 64 * PER + j * 64 + lane);
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < kPer; ++j) {
+            for (int j = 0; j < PER; ++j) {
                 const int k = j * kBlock + (int)threadIdx.x;
                 if (k < m) idx_out[dst[j]] = s[k];
             }
@@ -319,14 +320,30 @@ __global__ void k_bucket_check(const int32_t *start, int nb, int64_t max_per, Ct
         if ((int64_t)start[b + 1] - start[b] > max_per) raise_err(c.err, ERR_OVERFLOW);
 }
 
-int64_t chunks_of(int64_t n) { return std::max<int64_t>((n + kChunk - 1) / kChunk, 1); }
-
 // Passes, and the bits of each, for nb buckets.
 void plan(int nb, int &passes, int &bits) {
     int all = 1;
     while ((int64_t(1) << all) < nb) ++all;
     passes = all <= 16 ? 2 : 4;
     bits = (all + passes - 1) / passes;
+}
+
+// Particles per thread of a chunk: few where the sort is short, so that there
+// are chunks for the chip, more where the runs of a digit count, and twice as
+// many with more than 64 digits. Input in no order / sorted, with 2, 4, 8 and 16
+// particles, us: 512 x 512 cells mixed, n = 0.1M (8-bit keys) 33, 36, 49, 79 / 39, 43,
+// 57, 87; 1.0M 53, 54, 65, 91 / 60, 63, 72, 99; 4.0M 153, 136, 146, 139 / 140, 137, 158,
+// 148; 16.8M 749, 658, 594, 613 / 687, 592, 589, 649; 16-bit keys (2048 x 2048 cells in
+// 8 x 8 tiles): 1.0M 109, 83, 75, 97 / 72, 71, 78, 104; 16.8M 1823, 1147, 860, 770 /
+// 881, 668, 602, 638.
+int per_of(int64_t n, int bits) {
+    const int per = n < (int64_t(1) << 19) ? 2 : n < (int64_t(1) << 23) ? 4 : 8;
+    return bits > 6 ? 2 * per : per;
+}
+
+int64_t chunks_of(int64_t n, int bits) {
+    const int64_t chunk = (int64_t)kBlock * per_of(n, bits);
+    return std::max<int64_t>((n + chunk - 1) / chunk, 1);
 }
 
 }  // namespace
@@ -340,7 +357,7 @@ void plan(int nb, int &passes, int &bits) {
 int64_t sort_tallies(int64_t n, int nb) {
     int passes, bits;
     plan(nb, passes, bits);
-    return chunks_of(n) << bits;
+    return chunks_of(n, bits) << bits;
 }
 
 int64_t sort_groups(int64_t n, int nb) { return (sort_tallies(n, nb) + kScan - 1) / kScan; }
@@ -350,26 +367,35 @@ hipError_t launch_sort(const Geo &g, bool mixed, const Parts &p, const Parts &tm
                        const CtxDev &c, hipStream_t s) {
     int passes, bits;
     plan(g.nbuckets, passes, bits);
-    const int chunks = (int)chunks_of(n);
+    const int chunks = (int)chunks_of(n, bits);
     const int64_t m = (int64_t)chunks << bits;
     const int groups = (int)((m + kScan - 1) / kScan);
-    const size_t sh = (size_t)kChunk * (mixed ? 4 : 8);
-    for (int k = 0; k < passes && n > 0; ++k) {
+    auto pass = [&](auto per, int k) {
+        constexpr int PER = decltype(per)::value;
+        const size_t sh = (size_t)kBlock * PER * (mixed ? 4 : 8);
         const Parts &in = k & 1 ? tmp : p, &out = k & 1 ? p : tmp;
         const int32_t *iin = k == 0 ? nullptr : k & 1 ? idx : perm;
         int32_t *iout = !perm ? nullptr : k & 1 ? perm : idx;
         APIC_SORT_DISPATCH(g, mixed, {
             if (k == 0)
-                hipLaunchKernelGGL((k_sort_count<MIX, DIM, VDIM, true>), dim3(chunks), dim3(kBlock), 0, s, g, in, n, 0,
-                                   bits, cnt, c);
+                hipLaunchKernelGGL((k_sort_count<MIX, DIM, VDIM, PER, true>), dim3(chunks), dim3(kBlock), 0, s, g, in,
+                                   n, 0, bits, cnt, c);
             else
-                hipLaunchKernelGGL((k_sort_count<MIX, DIM, VDIM, false>), dim3(chunks), dim3(kBlock), 0, s, g, in, n,
-                                   k * bits, bits, cnt, c);
+                hipLaunchKernelGGL((k_sort_count<MIX, DIM, VDIM, PER, false>), dim3(chunks), dim3(kBlock), 0, s, g, in,
+                                   n, k * bits, bits, cnt, c);
             hipLaunchKernelGGL(k_sort_scan, dim3(groups), dim3(kBlock), 0, s, cnt, m, part);
-            hipLaunchKernelGGL(k_sort_base, dim3(1), dim3(kBlock), 0, s, part, groups);
-            hipLaunchKernelGGL((k_sort_move<MIX, DIM, VDIM>), dim3(chunks), dim3(kBlock), sh, s, g, in, out, n,
+            if (groups > 1) hipLaunchKernelGGL(k_sort_base, dim3(1), dim3(kBlock), 0, s, part, groups);
+            hipLaunchKernelGGL((k_sort_move<MIX, DIM, VDIM, PER>), dim3(chunks), dim3(kBlock), sh, s, g, in, out, n,
                                k * bits, bits, cnt, part, iin, iout, c);
         });
+    };
+    for (int k = 0; k < passes && n > 0; ++k) {
+        switch (per_of(n, bits)) {
+        case 2: pass(std::integral_constant<int, 2>{}, k); break;
+        case 4: pass(std::integral_constant<int, 4>{}, k); break;
+        case 8: pass(std::integral_constant<int, 8>{}, k); break;
+        default: pass(std::integral_constant<int, 16>{}, k);
+        }
     }
     APIC_SORT_DISPATCH(g, mixed,
                        hipLaunchKernelGGL((k_sort_table<MIX, DIM, VDIM>),
