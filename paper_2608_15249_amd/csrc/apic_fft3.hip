@@ -28,29 +28,12 @@
 // done in LDS; every global read and write covers runs of at least 64
 // bytes.
 #include "apic_fftlds.h"
+#include "apic_index.h"
 
 namespace apic {
 namespace {
 
-// Work split (all powers of two): rows per x workgroup, planes per y
-// workgroup, ky values per z workgroup.
-struct Split3 {
-    int Y, ZB, KY;
-};
-
-inline Split3 split3(const Geo &g) {
-    Split3 s;
-    // small workgroups, several to a CU, so that the loads of some overlap the passes
-    // of others (64-byte runs in the y launches; solve and gradient at 128^3 / 32^3 in
-    // us: 85.7 / 26.4 with 16 rows, 8 planes, 8 ky, 83.2 / 24.4 with 8, 4, 4; 89.6 with
-    // 32 rows, 90.6 with 16 planes, 89.3 with 16 ky, 93.4 with 2)
-    s.Y = 8;
-    if (s.Y > g.ny) s.Y = g.ny;
-    s.ZB = g.nz <= 128 ? 4 : 8;
-    s.KY = 4;
-    if (s.KY > g.ny) s.KY = g.ny;
-    return s;
-}
+inline Split3 split3(const Geo &g) { return split3_of(g.nx, g.ny, g.nz); }
 
 // LDS: two buffers of (Y/2) nx complex.
 template <bool MIX>

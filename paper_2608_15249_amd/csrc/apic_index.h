@@ -1,7 +1,7 @@
 // Rules that are plain functions of counts, without any HIP type, so that the
-// CPU tests can go through them: which calls keep the particles in pages, and
-// the indices of kernels whose rounds start before a bucket's first particle or
-// end behind its last.
+// CPU tests can go through them: which calls keep the particles in pages, the
+// indices of kernels whose rounds start before a bucket's first particle or end
+// behind its last, and the work split of the 3D field solve.
 #pragma once
 
 namespace apic {
@@ -27,5 +27,32 @@ constexpr int copy_slot(int k, int count) { return k < 0 ? 0 : k < count ? k : c
 // use). k is unsigned and counts from the bucket's start: there are up to
 // 2^31 - 2 particles, and the places run past a bucket by a round.
 constexpr int ahead_index(int first, unsigned k, unsigned count) { return first + (int)(k < count ? k : count - 1); }
+
+// Work split of the 3D field solve's launches (powers of two): rows per x
+// workgroup, planes per y workgroup, ky values per z workgroup.
+struct Split3 {
+    int Y, ZB, KY;
+};
+
+// Small workgroups, several to a CU, so that the loads of some overlap the passes
+// of others: about 512 points each (two per thread), in at least 8 rows or 4 lines
+// (64-byte runs in the y launches) and at most 16, or 8 on grids so small that the
+// chip is short of workgroups. Lines shorter than 128 points take more than the
+// least: with 8 rows, 4 planes and 4 ky for every grid, threads were left without a
+// point. Solve and gradient, mixed, us, with (16 rows, or 8 from 256 points per row
+// on; 8 planes; 8 ky, or 4 above 128 planes) / (8; 4, or 8 above 128 planes; 4) /
+// this rule: 128^3 92.7, 90.6, 90.0; 32^3 25.8, 25.7, 25.7 (26.4 with 16); 256 x 64 x
+// 32 46.6, 52.3, 44.5; 64 x 256 x 32 51.0, 56.9, 50.1; 32 x 64 x 256 55.7, 58.5, 54.4;
+// 128 x 128 x 32 48.0, 52.7, 47.0; 256 x 256 x 64 153, 164, 151; 16 x 256 x 256 103,
+// 108, 91; 256^3 (8 planes for its longer runs along z) 580, 583, 583.
+constexpr int split_lines(int wanted, int least, int cap, int most) {
+    const int n = wanted < least ? least : wanted > cap ? cap : wanted;
+    return n < most ? n : most;
+}
+constexpr Split3 split3_of(int nx, int ny, int nz) {
+    const int cap = nx * ny * nz <= 32768 ? 8 : 16;
+    return Split3{split_lines(1024 / nx, 8, cap, ny),   // (two rows to a line)
+                  split_lines(512 / ny, nz <= 128 ? 4 : 8, cap, nz), split_lines(512 / nz, 4, cap, ny)};
+}
 
 }  // namespace apic

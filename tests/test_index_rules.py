@@ -67,3 +67,30 @@ def test_places_ahead_at_the_largest_bucket(tmp_path):
                 }
             }
     """)
+
+
+def test_work_split_of_the_3d_field_solve(tmp_path):
+    """Every power-of-two grid: the splits divide it, the tiles fit 64 KiB of LDS, and no workgroup has fewer than 512 points
+    (two per thread) unless sixteen lines (eight on grids up to 32768 nodes) hold no more or the grid has no more."""
+    run(tmp_path, """
+    auto lines = [](const char *what, int got, int n, int most, int nx, int ny, int nz) {
+        const int cap = nx * ny * nz <= 32768 ? 8 : 16, want = 512 / n > cap ? cap : 512 / n;
+        const bool ok = got > 0 && most % got == 0 && (got >= want || got == most);
+        if (!ok) std::printf("%s: %d lines of %d (%d x %d x %d)\\n", what, got, n, nx, ny, nz);
+        return ok;
+    };
+    for (int nx = 4; nx <= 256; nx *= 2)
+        for (int ny = 4; ny <= 256; ny *= 2)
+            for (int nz = 4; nz <= 256; nz *= 2) {
+                const Split3 s = split3_of(nx, ny, nz);
+                const int cap = nx * ny * nz <= 32768 ? 8 : 16;
+                if (s.Y % 2 || ny % s.Y || (s.Y < cap && s.Y < ny && s.Y / 2 * nx < 512)) {
+                    std::printf("x: %d rows of %d\\n", s.Y, nx);
+                    return 1;
+                }
+                if (!lines("y", s.ZB, ny, nz, nx, ny, nz) || !lines("z", s.KY, nz, ny, nx, ny, nz)) return 1;
+                if (16 * s.Y * nx > 65536 || 32 * s.ZB * ny > 65536 || 32 * s.KY * nz > 65536 ||
+                    16 * s.Y * (nx + nx / 2 + 1) > 65536)
+                    return 1;
+            }
+    """)
