@@ -99,6 +99,12 @@ struct FinArgs {
     int sd;
 };
 
+// Bytes of particles that stay in the memory-side cache (256 MB) from one pass to the next.
+constexpr int64_t kCachedBytes = int64_t(208) << 20;
+// Bytes of n particles' state.
+inline int64_t particle_state_bytes(const Geo &g, bool mixed, int64_t n) {
+    return n * (mixed ? 4 * (1 + g.dim + g.vdim) : 8 * (g.dim + g.vdim));
+}
 constexpr int kMaxSpecBlocks = 16384;  // per-block partials of the field energies
 // Waves per workgroup of the fused step passes (tally, offsets, push): one
 // workgroup per bucket, so this sets the waves a tile's particles share.

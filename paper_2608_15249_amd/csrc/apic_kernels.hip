@@ -154,10 +154,8 @@ __global__ void __launch_bounds__(kBlock) k_deposit_direct(Geo g, Parts p, int64
 }
 
 // Tiled forms of the deposit and of the gather + push: one workgroup per
-// bucket, kAhead particles per thread loaded before the first is used.
-constexpr int kAhead = 4;
-
-template <bool MIX, int DIM, int VDIM>
+// bucket, AHEAD particles per thread loaded before the first is used.
+template <bool MIX, int DIM, int VDIM, int AHEAD>
 __global__ void __launch_bounds__(kBlock) k_deposit_tiled(Geo g, Parts p, const int32_t *bstart,
                                                           typename AccOf<MIX>::T *acc, CtxDev c) {
     using A = typename AccOf<MIX>::T;
@@ -174,13 +172,14 @@ __global__ void __launch_bounds__(kBlock) k_deposit_tiled(Geo g, Parts p, const 
     for (int t = threadIdx.x; t < wx * wy * wz; t += blockDim.x) sA[t] = (A)0;
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    const unsigned count = i1 - i0, ahead = kAhead * blockDim.x;
+    const unsigned count = i1 - i0, ahead = AHEAD * blockDim.x;
     for (unsigned k0 = threadIdx.x; k0 < count; k0 += ahead) {
-        Raw<MIX> r[kAhead];
+        Raw<MIX> r[AHEAD];
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, 0>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
+        for (int j = 0; j < AHEAD; ++j)
+            load_raw<MIX, DIM, 0, false>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
+        for (int j = 0; j < AHEAD; ++j) {
             if (k0 + j * blockDim.x >= count) break;
             Pt<MIX> q;
             if (!decode<MIX, DIM, 0>(r[j], g, q)) {
@@ -251,7 +250,7 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_direct(Geo g, Parts p, i
     }
 }
 
-template <bool MIX, int DIM, int VDIM, bool HC>
+template <bool MIX, int DIM, int VDIM, bool HC, int AHEAD, bool MOVE>
 __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, const int32_t *bstart,
                                                               const typename Pt<MIX>::R *E, PushC pc,
                                                               CtxDev c) {
@@ -271,17 +270,21 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, co
         load_e_tile<R, R, DIM>(sE, E, g, x0, y0, ex_w, ey_w);
     __syncthreads();
     const int i0 = min(max(bstart[b], 0), g.np), i1 = min(max(bstart[b + 1], i0), g.np);
-    const unsigned count = i1 - i0, ahead = kAhead * blockDim.x;
+    const unsigned count = i1 - i0, ahead = AHEAD * blockDim.x;
     for (unsigned k0 = threadIdx.x; k0 < count; k0 += ahead) {
-        Raw<MIX> r[kAhead];
+        Raw<MIX> r[AHEAD];
+        if constexpr (AHEAD > 1) {
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) load_raw<MIX, DIM, VDIM>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
+            for (int j = 0; j < AHEAD; ++j)
+                load_raw<MIX, DIM, VDIM, false>(p, ahead_index(i0, k0 + j * blockDim.x, count), r[j]);
+        }
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            if (k0 + j * blockDim.x >= count) break;
+        for (int j = 0; j < AHEAD; ++j) {
+            if (AHEAD > 1 && k0 + j * blockDim.x >= count) break;
             const int i = i0 + (int)(k0 + j * blockDim.x);
             Pt<MIX> q;
-            if (!decode<MIX, DIM, VDIM>(r[j], g, q)) {
+            const bool ok = AHEAD > 1 ? decode<MIX, DIM, VDIM>(r[j], g, q) : load_pt<MIX, DIM, VDIM>(p, i, g, q);
+            if (!ok) {
                 raise_err(c.err, ERR_DOMAIN);
                 continue;
             }
@@ -307,9 +310,9 @@ __global__ void __launch_bounds__(kBlock) k_gather_push_tiled(Geo g, Parts p, co
                 }
             }
             int sx, sy, sz;
-            if (!push_move<MIX, DIM, VDIM, HC>(q, g, pc, ex, ey, ez, pc.move != 0, sx, sy, sz))
+            if (!push_move<MIX, DIM, VDIM, HC>(q, g, pc, ex, ey, ez, MOVE, sx, sy, sz))
                 raise_err(c.err, ERR_DOMAIN);
-            store_moved<MIX, DIM, VDIM>(p, i, q, pc.move != 0);
+            store_moved<MIX, DIM, VDIM>(p, i, q, MOVE);
         }
     }
 }
@@ -1388,14 +1391,36 @@ hipError_t launch_copy_bytes(void *dst, const void *src, int64_t bytes, hipStrea
 }
 
 
+// Whether the tiled kernels load four particles per thread ahead of their use, through
+// the caches (past them, mixed states of 56 to 112 MB lost: 2D half push 26.0 and 31.6 us, 3D
+// 33.1 and 41.2; beyond the caches 2D 124 and 127, 3D 156 and 153).
+// The deposit: with two or more per thread. One and four ahead, us: 39 particles per bucket 6.0
+// and 6.2, 146 8.9 and 9.3, 537 11.9 and 11.4, 3906 16.8 and 15.7, 16384 45.4 and 40.0; 3D
+// 8192 82.6 and 74.4.
+// The push: where the buckets are so few that their waves leave the memory idle, with four or
+// more per thread. Half push, 1D in 128 buckets mixed 105 and 53.9, 2D in 256 12.0 and 11.5, FP64
+// 23.8 and 17.9, 3D in 128 FP64 46.7 and 33.0; but 2D in 1024 24.7 and 25.5, 16.8M particles 124
+// and 136, FP64 222 and 237. With a move the state is also written, behind the loads: 1D in 128 91.9 and
+// 67.2, 3D in 128 FP64 51.7 and 41.2, but 2D in 1024 181 and 202 (232 past the caches), FP64 289 and
+// 316, 3D in 2048 mixed 237 and 297 past the caches.
+static bool deposit_ahead(const Geo &g, int64_t n) { return n >= 2 * (int64_t)kBlock * g.nbuckets; }
+static bool push_ahead(const Geo &g, int64_t n) {
+    return g.nbuckets < 2 * cu_count() && n >= 4 * (int64_t)kBlock * g.nbuckets;
+}
+
 hipError_t launch_deposit(const Geo &g, bool mixed, const Parts &p, int64_t n, const int32_t *bstart, void *acc,
                           const CtxDev &c, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (bstart) {
         size_t sh = tile_acc_bytes(g, 0);
-        APIC_DISPATCH(g, mixed,
-                      hipLaunchKernelGGL((k_deposit_tiled<MIX, DIM, VDIM>), dim3(grid_for_buckets(g.nbuckets)),
-                                         dim3(kBlock), sh, s, g, p, bstart, (typename AccOf<MIX>::T *)acc, c));
+        APIC_DISPATCH(g, mixed, {
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3(grid_for_buckets(g.nbuckets)), dim3(kBlock), sh, s, g, p, bstart,
+                                   (typename AccOf<MIX>::T *)acc, c);
+            };
+            if (deposit_ahead(g, n)) go(k_deposit_tiled<MIX, DIM, VDIM, 4>);
+            else go(k_deposit_tiled<MIX, DIM, VDIM, 1>);
+        });
     } else {
         APIC_DISPATCH(g, mixed,
                       hipLaunchKernelGGL((k_deposit_direct<MIX, DIM, VDIM>), dim3(blocks_for(n)), dim3(kBlock), 0, s,
@@ -1409,9 +1434,19 @@ hipError_t launch_gather_push(const Geo &g, bool mixed, const Parts &p, int64_t 
     if (n <= 0) return hipSuccess;
     if (bstart) {
         size_t sh = tile_e_bytes(g, mixed);
-        APIC_DISPATCH(g, mixed,
-                      hipLaunchKernelGGL((k_gather_push_tiled<MIX, DIM, VDIM, HC>), dim3(grid_for_buckets(g.nbuckets)),
-                                         dim3(kBlock), sh, s, g, p, bstart, (const typename Pt<MIX>::R *)E, pc, c));
+        APIC_DISPATCH(g, mixed, {
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3(grid_for_buckets(g.nbuckets)), dim3(kBlock), sh, s, g, p, bstart,
+                                   (const typename Pt<MIX>::R *)E, pc, c);
+            };
+            if (push_ahead(g, n)) {
+                if (pc.move) go(k_gather_push_tiled<MIX, DIM, VDIM, HC, 4, true>);
+                else go(k_gather_push_tiled<MIX, DIM, VDIM, HC, 4, false>);
+            } else {
+                if (pc.move) go(k_gather_push_tiled<MIX, DIM, VDIM, HC, 1, true>);
+                else go(k_gather_push_tiled<MIX, DIM, VDIM, HC, 1, false>);
+            }
+        });
     } else {
         APIC_DISPATCH(g, mixed,
                       hipLaunchKernelGGL((k_gather_push_direct<MIX, DIM, VDIM, HC>), dim3(blocks_for(n)), dim3(kBlock), 0,

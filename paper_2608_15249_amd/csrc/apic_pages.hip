@@ -42,7 +42,6 @@ namespace apic {
 
 namespace {
 
-constexpr int64_t kPageCached = int64_t(208) << 20;   // bytes of particles that stay in the caches between steps
 constexpr int kPageScanMax = 4096;   // buckets up to which the exchange scans the counts itself
 
 // ---- page table of a call ------------------------------------------------------
@@ -1339,8 +1338,7 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
     // 100, 216 MB 163 and 157, 288 MB 186 and 197; walls 160 MB 126 and 122, 240 MB
     // 184 and 189. 3D mixed 56 MB 173 and 170, 168 MB 225 and 230, 470 MB 384 and 431.
     // (The electromagnetic push is not bound by its pages: 201 MB 156 and 158.)
-    const int64_t state = n * (mixed ? 4 * (1 + g.dim + g.vdim) : 8 * (g.dim + g.vdim));
-    const bool cached = state <= kPageCached;
+    const bool cached = particle_state_bytes(g, mixed, n) <= kCachedBytes;
     const size_t tile = tile_acc_bytes(g, g.halo) + tile_e_bytes(g, mixed);
     const size_t sh = f.E ? std::max(tile, (size_t)(g.nx + 2 * kBlock) * sizeof(double)) : tile;
     APIC_DISPATCH(g, mixed, {

@@ -243,15 +243,24 @@ template <> struct Raw<false> {
     double x, y, z, vx, vy, vz;
 };
 
-template <bool MIX, int DIM, int VDIM>
+template <bool MIX, int DIM, int VDIM, bool NT = MIX>
 __device__ __forceinline__ void load_raw(const Parts &s, int i, Raw<MIX> &r) {
     // each particle is read once per pass, in whole 128-byte lines per wave
-    // (the passes align their chunks). The mixed state loads with the
-    // nontemporal hint: measured at 512^2 (2D2V), 1024^2 (2D3V) and 128^3,
-    // it was faster or equal; the FP64 state loads through the caches (the
+    // (the passes align their chunks). The mixed state of the step's passes loads
+    // with the nontemporal hint (NT): measured at 512^2 (2D2V), 1024^2 (2D3V) and
+    // 128^3, it was faster or equal; the FP64 state loads through the caches (the
     // hint made its push 5% slower). Nontemporal stores of the scattered
     // destination slots made the mixed push 1.6x slower.
-    if constexpr (MIX) {
+    static_assert(MIX || !NT, "the FP64 state loads through the caches");
+    if constexpr (MIX && !NT) {
+        r.c = s.cell[i];
+        r.ox = s.ox[i];
+        r.oy = (DIM >= 2) ? s.oy[i] : 0.0f;
+        r.oz = (DIM == 3) ? s.oz[i] : 0.0f;
+        r.vx = (VDIM >= 1) ? ((const float *)s.vx)[i] : 0.0f;
+        r.vy = (VDIM >= 2) ? ((const float *)s.vy)[i] : 0.0f;
+        r.vz = (VDIM >= 3) ? ((const float *)s.vz)[i] : 0.0f;
+    } else if constexpr (MIX) {
         r.c = __builtin_nontemporal_load(&s.cell[i]);
         r.ox = __builtin_nontemporal_load(&s.ox[i]);
         r.oy = (DIM >= 2) ? __builtin_nontemporal_load(&s.oy[i]) : 0.0f;
