@@ -24,7 +24,7 @@ class FieldEnergyRun:
         self.torch = torch
         self.ctx = Context(dim=dim, vdim=vdim, nx=nx, ny=ny, nz=nz, lx=lx, ly=ly, lz=lz, dt=dt, n=n, qm=qm,
                            rho_ion=rho_ion, bz=bz, precision=precision, tile=tile, device=device, pusher=pusher,
-                           c_light=c_light)
+                           c_light=c_light, max_workspace=0)   # (every step here has a workspace of its own)
         self.parts = Particles(self.ctx)
         self.nsteps, self.stride = int(nsteps), int(stride)
         ck, ws = self.ctx.adjoint_sizes(self.nsteps, self.stride)

@@ -82,3 +82,14 @@ def test_long_call_without_pages(torch, monkeypatch, how, precision):  # noqa: F
                 # sums of binary64 round by their order: 1e-16 amplified over nine steps by less than 1e4; the slots are
                 # the same as long as no particle's tile differs by it
                 assert np.max(np.abs(a[k] - b[k])) <= 1e-11 * max(1.0, np.max(np.abs(a[k]))), k
+
+
+def test_a_gradient_run_keeps_no_room_for_pages(torch):  # noqa: F811
+    """FieldEnergyRun steps in the adjoint workspace: its context asks for the least."""
+    from paper_2608_15249_amd.adjoint import FieldEnergyRun
+    kw = dict(dim=2, vdim=2, nx=32, ny=32, lx=32.0, ly=32.0, dt=0.1, n=20011, tile=(16, 16))
+    run = FieldEnergyRun(nsteps=4, stride=2, **kw)
+    full = paged._context(dict(dim=2, vdim=2, cells=(32, 32), tile=(16, 16)), 20011, "mixed")
+    assert run.ctx.ws.numel() < full.ws.numel()
+    full._check(full.L.apic_workspace_limit(full.h, 0))
+    assert run.ctx.ws.numel() == size(full)
