@@ -47,6 +47,7 @@ struct PageStep {
     int32_t *queue;                  // [npages] ring of free pages
     unsigned long long *head;        // [2] pages taken from and given to the ring so far
     int64_t npages;
+    int scanned;                     // ds and ps are k_page_scan's work already
     int32_t *live;                   // [1] particles not absorbed by a wall
     int32_t *done;                   // [1] buckets whose 1D push has ended, zero between the steps
     char *pool;                      // [npages] pages

@@ -511,8 +511,8 @@ __device__ __forceinline__ void advance_group(const Raw<MIX> *r, const Geo &g, c
 // leavers of the step before come in from the neighbours' lists. The new counts
 // are complete (the push added every stay and every leaver to its bucket), so
 // each workgroup sums those of the buckets before its own (a few KiB, cache
-// resident) for the bucket's list and page-table entries; SCANNED (more than
-// kPageScanMax buckets): k_page_scan has done it. Arrival i takes hole i while
+// resident) for the bucket's list and page-table entries; with more than
+// kPageScanMax buckets k_page_scan has done it (t.scanned). Arrival i takes hole i while
 // there are holes, then slot old + i - holes; a bucket that shrinks closes its
 // remaining holes with the particles beyond its new end.
 struct ExchangeLds {
@@ -525,7 +525,7 @@ struct ExchangeLds {
     uint32_t map[kBits / 32];
 };
 
-template <bool MIX, int DIM, int VDIM, bool SCANNED>
+template <bool MIX, int DIM, int VDIM>
 __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t n, int64_t max_per, const CtxDev &c,
                                 ExchangeLds &sh) {
     constexpr int kFar = Dir<DIM>::kFar, kStay = Dir<DIM>::kStay, kTab = Dir<DIM>::kTab;
@@ -564,7 +564,7 @@ __device__ void exchange_bucket(const Geo &g, const PageStep &t, int b, int64_t 
         if (np_new < np_old) sh.q = atomicAdd(&t.head[1], (unsigned long long)(np_old - np_new));
     }
     int pn, dn;   // the bucket's first entries now
-    if constexpr (SCANNED) {
+    if (t.scanned) {
         pn = t.ps[b];
         dn = t.ds[b];
         __syncthreads();
@@ -769,7 +769,7 @@ __device__ void field_by_last(const Geo &g, const PageStep &t, const PageField &
 // leavers to its own part of the bucket's list. FIRST: the particles come from
 // the caller's arrays (bucket b from bstart[b]), one by one, and go to the
 // same slots of the pages.
-template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool SCANNED, bool NT>
+template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool NT>
 __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>())) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
                                                             int64_t n, int64_t max_per, const double *E, const float *E32, PushC pc,
                                                             typename AccOf<MIX>::T *acc, double *part, PageField f, CtxDev c) {
@@ -808,7 +808,7 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
     }
     if constexpr (!FIRST) {
         __shared__ ExchangeLds sEx;
-        exchange_bucket<MIX, DIM, VDIM, SCANNED>(g, t, b, n, max_per, c, sEx);
+        exchange_bucket<MIX, DIM, VDIM>(g, t, b, n, max_per, c, sEx);
     }
     {
         int bx, by, bz;
@@ -1231,14 +1231,14 @@ __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>()
 }
 
 // ---- back to the caller's arrays --------------------------------------------------
-template <bool MIX, int DIM, int VDIM, bool SCANNED>
+template <bool MIX, int DIM, int VDIM>
 __global__ void __launch_bounds__(kBlock) k_page_end(Geo g, PageStep t, int64_t n, int64_t max_per, Parts dst,
                                                      int32_t *bstart, CtxDev c) {
     __shared__ ExchangeLds sEx;
     const int nb = g.nbuckets;
     const int b = bucket_of_block(nb);
     if (b >= nb) return;
-    exchange_bucket<MIX, DIM, VDIM, SCANNED>(g, t, b, n, max_per, c, sEx);
+    exchange_bucket<MIX, DIM, VDIM>(g, t, b, n, max_per, c, sEx);
     {
         const int count = t.cnt[b], dsb = t.ds[b], psb = t.ps[b];
         if (threadIdx.x == 0) {
@@ -1288,14 +1288,16 @@ hipError_t launch_page_begin(const Geo &g, const PageStep &t, int32_t *cnt3, int
     return hipGetLastError();
 }
 
-// The sums over the buckets before a push or a call's end, where the
-// workgroups do not take them themselves.
-static bool scan_apart(const Geo &g, const PageStep &t, int64_t n, int64_t max_per_bucket, const CtxDev &c,
-                       hipStream_t s) {
-    if (g.nbuckets <= kPageScanMax) return false;
-    hipLaunchKernelGGL(k_page_scan<false>, dim3(1), dim3(1024), 0, s, g.nbuckets, n, g.walls, max_per_bucket, nullptr,
-                       (int32_t *)t.cnt, t.ds, t.ps, c);
-    return true;
+// The step with the sums over the buckets before a push or a call's end taken
+// apart, where the workgroups do not take them themselves.
+static PageStep scan_apart(const Geo &g, const PageStep &step, int64_t n, int64_t max_per_bucket, const CtxDev &c,
+                           hipStream_t s) {
+    PageStep t = step;
+    t.scanned = g.nbuckets > kPageScanMax;
+    if (t.scanned)
+        hipLaunchKernelGGL(k_page_scan<false>, dim3(1), dim3(1024), 0, s, g.nbuckets, n, g.walls, max_per_bucket,
+                           nullptr, (int32_t *)t.cnt, t.ds, t.ps, c);
+    return t;
 }
 
 // Threads per bucket: 256, or twice that with at most two buckets per CU, which
@@ -1305,12 +1307,12 @@ static bool scan_apart(const Geo &g, const PageStep &t, int64_t n, int64_t max_p
 // 4.2M mixed between walls in 1024 buckets 73.7 us with 256, 82.8 with 512.
 int push_block(const Geo &g) { return g.nbuckets <= 2 * cu_count() ? kPagePushMax : kBlock; }
 
-hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const Parts *src, const int32_t *bstart,
+hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &step, const Parts *src, const int32_t *bstart,
                             int64_t n, int64_t max_per_bucket, const double *E, const float *E32, const PushC &pc,
                             void *acc, double *part, const PageField &f, const CtxDev &c, hipStream_t s) {
     const dim3 grid(grid_for_buckets(g.nbuckets));
     const Parts from = src ? *src : Parts{};
-    const bool scanned = !src && scan_apart(g, t, n, max_per_bucket, c, s);
+    const PageStep t = src ? step : scan_apart(g, step, n, max_per_bucket, c, s);
     if (g.em) {
         const size_t sh = em_j_tile_bytes(g) + em_f_tile_bytes(g, mixed);
         auto go = [&](auto kern, auto *accp) {
@@ -1319,16 +1321,15 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         };
         unsigned long long *am = (unsigned long long *)acc;
         double *ad = (double *)acc;
-        auto pick = [&](auto first, auto sc) {
-            constexpr bool F = decltype(first)::value, S = decltype(sc)::value;
-            if (mixed && g.hc) go(k_page_push<true, 2, 3, true, true, false, F, S, true>, am);
-            else if (mixed) go(k_page_push<true, 2, 3, false, true, false, F, S, true>, am);
-            else if (g.hc) go(k_page_push<false, 2, 3, true, true, false, F, S, true>, ad);
-            else go(k_page_push<false, 2, 3, false, true, false, F, S, true>, ad);
+        auto pick = [&](auto first) {
+            constexpr bool F = decltype(first)::value;
+            if (mixed && g.hc) go(k_page_push<true, 2, 3, true, true, false, F, true>, am);
+            else if (mixed) go(k_page_push<true, 2, 3, false, true, false, F, true>, am);
+            else if (g.hc) go(k_page_push<false, 2, 3, true, true, false, F, true>, ad);
+            else go(k_page_push<false, 2, 3, false, true, false, F, true>, ad);
         };
-        if (src) pick(std::true_type{}, std::false_type{});
-        else if (scanned) pick(std::false_type{}, std::true_type{});
-        else pick(std::false_type{}, std::false_type{});
+        if (src) pick(std::true_type{});
+        else pick(std::false_type{});
         return hipGetLastError();
     }
     // Below 3D, pages that the memory-side cache (256 MB) can hold from step to step
@@ -1351,16 +1352,14 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
             constexpr bool ROT = decltype(rot)::value;
             if constexpr (DIM < 3) {
                 if (cached) {
-                    if (scanned) go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true, false>);
-                    else go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false, false>);
+                    go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false>);
                     return;
                 }
             }
-            if (scanned) go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true, true>);
-            else go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, false, true>);
+            go(k_page_push<MIX, DIM, VDIM, HC, false, ROT, false, true>);
         };
         if (src) {
-            go(k_page_push<MIX, DIM, VDIM, HC, false, false, true, false, true>);
+            go(k_page_push<MIX, DIM, VDIM, HC, false, false, true, true>);
         } else if constexpr (VDIM >= 2 && !HC) {
             if (pc.t != 0.0) pick(std::true_type{});
             else pick(std::false_type{});
@@ -1377,18 +1376,13 @@ hipError_t launch_page_push(const Geo &g, bool mixed, const PageStep &t, const P
         else APIC_DISPATCH_2D(g, mixed, __VA_ARGS__);                                                       \
     } while (0)
 
-hipError_t launch_page_end(const Geo &g, bool mixed, const PageStep &t, int64_t n, int64_t max_per_bucket,
+hipError_t launch_page_end(const Geo &g, bool mixed, const PageStep &step, int64_t n, int64_t max_per_bucket,
                            const Parts &dst, int32_t *bstart, const CtxDev &c, hipStream_t s) {
     const dim3 grid(grid_for_buckets(g.nbuckets));
-    const bool scanned = scan_apart(g, t, n, max_per_bucket, c, s);
-    APIC_PAGE_DISPATCH(g, mixed, {
-        if (scanned)
-            hipLaunchKernelGGL((k_page_end<MIX, DIM, VDIM, true>), grid, dim3(kBlock), 0, s, g, t, n, max_per_bucket,
-                               dst, bstart, c);
-        else
-            hipLaunchKernelGGL((k_page_end<MIX, DIM, VDIM, false>), grid, dim3(kBlock), 0, s, g, t, n, max_per_bucket,
-                               dst, bstart, c);
-    });
+    const PageStep t = scan_apart(g, step, n, max_per_bucket, c, s);
+    APIC_PAGE_DISPATCH(g, mixed,
+                       hipLaunchKernelGGL((k_page_end<MIX, DIM, VDIM>), grid, dim3(kBlock), 0, s, g, t, n,
+                                          max_per_bucket, dst, bstart, c));
     return hipGetLastError();
 }
 
