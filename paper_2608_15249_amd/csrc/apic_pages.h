@@ -6,7 +6,8 @@
 
 namespace apic {
 
-// Particle slots of a page: what a wave reads and writes at a time, 2 to 5 KiB.
+// Particle slots of a page: what a wave reads and writes at a time, 1.5 KiB (mixed
+// 1D1V) to 6 KiB (FP64 3D3V).
 // Pages of 256 were slower where they are a power of two of bytes (FP64 2D2V,
 // 8 KiB: the push at 512 x 512, 16.8M particles 276 us against 235) and a
 // little slower elsewhere (mixed 2D3V, 6 KiB: 350 against 345 us at 1024 x 1024,

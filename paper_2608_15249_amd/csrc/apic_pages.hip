@@ -23,14 +23,15 @@
 // with k_page_end, which copies the pages back to the caller's arrays in
 // bucket order. The order inside a bucket is a function of the order at the
 // call's start alone: leavers are listed in wave, chunk, lane order, arrivals
-// are dealt in direction order; only far arrivals take slots in arrival order,
-// and which page a bucket gets from the queue decides no result.
+// are dealt in direction order; only far arrivals take slots in the order in which
+// they joined their chains, and which page a bucket gets from the queue decides no
+// result.
 //
 // Magnetized 2D3V, 1024 x 1024 cells, 33.5M mixed particles, 32 x 16 tiles: the
 // reordering step's count, scan and push took 16 + 6 + 418 us, the push with its
 // exchange 364 us (1.61 GB of state read and written: 4.4 TB/s, where a copy of
-// 1 GB on the same card runs at 5.07 TB/s and the push's own page traffic without
-// any arithmetic took 331 us).
+// 1 GB on the same card runs at 5.07 TB/s; the same push with the arithmetic left out,
+// in a copy of this file that is not kept, took 331 us).
 #include <algorithm>
 #include <type_traits>
 
@@ -762,13 +763,13 @@ __device__ void field_by_last(const Geo &g, const PageStep &t, const PageField &
     if (threadIdx.x == 0) *t.done = 0;
 }
 
-// One workgroup per bucket. Wave w takes the units w, w + nw, ... of 64 *
-// lane_parts consecutive slots: each lane loads 16 bytes of every array and
-// writes them back to the same place, whole lines both ways. No slot is
-// computed and no barrier stands in the loop; a wave appends the slots of its
-// leavers to its own part of the bucket's list. FIRST: the particles come from
-// the caller's arrays (bucket b from bstart[b]), one by one, and go to the
-// same slots of the pages.
+// One workgroup per bucket. A unit is one page: wave w takes the pages w, w + nw,
+// ... of the bucket, each lane kPage / 64 of a page's slots, and reads and writes
+// them in pieces of the record (16, 8 or 4 bytes a lane, whole lines both ways).
+// No slot is computed and no barrier stands in the loop; a wave appends the slots
+// of its leavers to its own part of the bucket's list. FIRST: the particles come
+// from the caller's arrays (bucket b from bstart[b]), one by one, and go to the
+// same slots of the pages. NT: the pages are read and written past the caches.
 template <bool MIX, int DIM, int VDIM, bool HC, bool EM, bool ROT, bool FIRST, bool NT>
 __global__ void __launch_bounds__(kPagePushMax, (push_waves_per_simd<MIX, DIM>())) k_page_push(Geo g, PageStep t, Parts src, const int32_t *bstart,
                                                             int64_t n, int64_t max_per, const double *E, const float *E32, PushC pc,
