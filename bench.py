@@ -68,6 +68,17 @@ def phase_breakdown(ctx, run, steps):
     return ms, max(nprof, 1)
 
 
+def entry_of(d, precision, tile):
+    """The precision's entry of a counter file at this tile: under the
+    precision's name, or with the tile behind it.  The autotuner's candidates
+    are within its noise of each other, so the files hold several tiles."""
+    for key in (precision, "%s_%s" % (precision, "x".join(map(str, tile)))):
+        e = d.get(key)
+        if e and list(e.get("tile", [])) == list(tile):
+            return e
+    return None
+
+
 def load_traffic(precision, workload, tile):
     """HBM bytes per push-pass launch from committed rocprofv3 counter runs,
     if they were taken on the current kernel source, workload and tile;
@@ -78,8 +89,8 @@ def load_traffic(precision, workload, tile):
     from paper_2608_15249_amd.rocprof_summary import kernel_source_sha
     try:
         d = json.load(open(p))
-        e = d.get(precision)
-        if not e or d.get("kernel_src_sha") != kernel_source_sha() or list(e.get("tile", [])) != list(tile):
+        e = entry_of(d, precision, tile)
+        if not e or d.get("kernel_src_sha") != kernel_source_sha():
             return None
         return float(e["hbm_bytes_per_launch"])
     except Exception:
@@ -103,8 +114,8 @@ def load_counters(precision, workload, tile):
     from paper_2608_15249_amd.rocprof_summary import kernel_source_sha
     try:
         d = json.load(open(p))
-        e = d.get(precision)
-        if not e or d.get("kernel_src_sha") != kernel_source_sha() or list(e.get("tile", [])) != list(tile):
+        e = entry_of(d, precision, tile)
+        if not e or d.get("kernel_src_sha") != kernel_source_sha():
             return None
         return e["per_launch"]
     except Exception:
