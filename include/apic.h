@@ -152,7 +152,7 @@ typedef struct {
 typedef struct apic_ctx apic_ctx;
 
 /* Create a context for one plasma of n_particles particles: validates the
- * descriptor, builds the FFT plans for 2D grids and allocates the context's
+ * descriptor, builds the FFT plans of the grids that use them and allocates the context's
  * own small device words. Returns APIC_EINVAL for an invalid descriptor. */
 apic_status apic_create(const apic_grid_desc *desc, int64_t n_particles, apic_ctx **out);
 void apic_destroy(apic_ctx *ctx);
@@ -190,8 +190,8 @@ double apic_q_macro(const apic_ctx *ctx);
 int apic_tile_size(const apic_ctx *ctx, int axis);
 
 /* Counting sort of the particles by bucket: key = tile-major bucket of each
- * particle's cell; stable radix passes (tallies, exclusive scan, scatter),
- * the bucket table read off the sorted keys, a gather. Particles end up
+ * particle's cell; stable radix passes (tallies, exclusive scan, a move of the
+ * particles), the bucket table read off the sorted keys. Particles end up
  * ordered by ascending bucket, in place; bucket_start is written; perm is
  * written when non-NULL. The order inside a bucket is unspecified. The paper
  * leaves the particle data structures to the application ("Example setup and

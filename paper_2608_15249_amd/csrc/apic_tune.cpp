@@ -3,8 +3,8 @@
 // own particles (the caller's arrays are only read).
 //
 // A setup call, never part of a timed loop: each trial allocates a scratch
-// copy of the particles and a context, runs two warm-up steps and times a few
-// more with HIP events on the caller's stream. The winner is kept in a
+// copy of the particles and a context, runs a few warm-up steps and times calls
+// of the caller's length with HIP events on the caller's stream. The winner is kept in a
 // process-wide cache keyed by the problem's shape, so a later call with the
 // same shape returns at once.
 #include "apic.h"
